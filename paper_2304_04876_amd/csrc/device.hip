@@ -558,6 +558,10 @@ static void check_status(Device &D, int *d_status, int count, hipStream_t s, con
 }
 
 
+// Largest bandwidth the band factors are accepted with (LDS of a panel of 16
+// columns of that height, the limit the callers' sizes are checked against).
+static int chol_max_band(const Device &D) { return std::max(1, int((D.max_lds / sizeof(double) - 16 * 18) / 17)); }
+
 // Replaces the 64x64 diagonal blocks of the band factors of every subdomain
 // whose band holds whole triangles by their inverses (k_band_invert_diag);
 // rows_h: host row offsets of the subdomains, bw_h: host bandwidths.
@@ -576,11 +580,9 @@ static int invert_diagonal_blocks(Device &D, double *band, const int64_t *off, c
         bp[i + 1] = bp[i] + (inv ? (n + BS_NB - 1) / BS_NB : 0);
     }
     if (bp[np] == 0) return kinds;
-    const size_t lds = sizeof(double) * 2 * BS_NB * (BS_NB + 1);
-    if (lds > D.max_lds) throw DevError{GDSW_ERR_INTERNAL, "LDS too small for the diagonal-block inverses"};
     int64_t *d_bp = D.setup_scratch<int64_t>(tag, int64_t(bp.size()));
     HIPCHK(hipMemcpyAsync(d_bp, bp.data(), sizeof(int64_t) * bp.size(), hipMemcpyHostToDevice, s));
-    hipLaunchKernelGGL(k_band_invert_diag, dim3(unsigned(bp[np])), dim3(64), lds, s, band, off, bw, rptr, d_bp, np);
+    hipLaunchKernelGGL(k_band_invert_diag, dim3(unsigned(bp[np])), dim3(64), 0, s, band, off, bw, rptr, d_bp, np);
     HIPCHK(hipGetLastError());
     HIPCHK(hipStreamSynchronize(s));
     D.setup_release(d_bp, sizeof(int64_t) * bp.size());
@@ -796,10 +798,9 @@ static void factor_band(gdsw_handle_s *h, int *d_status, hipStream_t s) {
         if (!D.band_off) D.band_off = D.upload(S.band_off, s);
         if (!D.bw) D.bw = D.upload(S.bw, s);
         if (!D.queue) D.queue = D.alloc<int>(2 * QUEUE_HALF);
-        const size_t lds = sizeof(double) * (CH_NB * CH_LD + CH_NB + size_t(std::max(S.max_bw, 1)) * CH_LD);
-        if (lds > D.max_lds)
+        if (chol_max_band(D) < S.max_bw)
             throw DevError{GDSW_ERR_INVALID_ARG, "local bandwidth too large for the banded Cholesky"};
-        hipLaunchKernelGGL(k_band_chol<256>, dim3(S.np), dim3(256), lds, s, band64, D.band_off, D.bw, D.ov_ptr,
+        hipLaunchKernelGGL(k_band_chol<512>, dim3(S.np), dim3(512), 0, s, band64, D.band_off, D.bw, D.ov_ptr,
                            d_status);
         HIPCHK(hipGetLastError());
         check_status(D, d_status, S.np, s, "banded Cholesky");
@@ -1002,9 +1003,8 @@ static void coarse_numeric(gdsw_handle_s *h, hipStream_t s) {
         const int64_t ne = int64_t(S.ibscat_src.size());
         hipLaunchKernelGGL(k_gather_vals, dim3(nblocks(ne, 256, 65536)), dim3(256), 0, s, D.val, d_src, d_dst, iband,
                            ne, (const double *)nullptr, D.arow, D.col);
-        const size_t lds = sizeof(double) * (CH_NB * CH_LD + CH_NB + size_t(std::max(S.max_ibw, 1)) * CH_LD);
-        if (lds > D.max_lds) throw DevError{GDSW_ERR_INVALID_ARG, "interior bandwidth too large"};
-        hipLaunchKernelGGL(k_band_chol<256>, dim3(S.np), dim3(256), lds, s, iband, d_ioff, d_ibw, d_int_ptr, d_status);
+        if (chol_max_band(D) < S.max_ibw) throw DevError{GDSW_ERR_INVALID_ARG, "interior bandwidth too large"};
+        hipLaunchKernelGGL(k_band_chol<512>, dim3(S.np), dim3(512), 0, s, iband, d_ioff, d_ibw, d_int_ptr, d_status);
         HIPCHK(hipGetLastError());
         check_status(D, d_status, S.np, s, "interior Cholesky");
         const int ikinds = invert_diagonal_blocks(D, iband, d_ioff, d_ibw, d_int_ptr, S.int_ptr, S.ibw, S.np,

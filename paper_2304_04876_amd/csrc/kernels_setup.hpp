@@ -4,6 +4,9 @@
 // and its inverse.
 #pragma once
 
+#include <type_traits>
+#include <utility>
+
 #include "kernels_common.hpp"
 
 namespace gdsw {
@@ -213,99 +216,494 @@ __global__ void k_ilu_pack(const int64_t *__restrict__ ov_ptr, const int64_t *__
 }
 
 // ---------------------------------------------------------------------------
+// FP64 matrix instructions (16x16x4).  Lane l = 16 g + i holds A(i, k) and
+// B(k, i) for k = g, and of the 16x16 result D(g + 4 v, i) in value v.  The
+// result is that of four multiply-adds in ascending k, each rounded (checked
+// bit for bit, subnormal results included), so that sums over k taken four at
+// a time in ascending order have the bits of a scalar loop.  A sum over 16
+// values of k: instruction q takes k = 4 q + g, a lane's four operands stand
+// four columns apart.
+typedef double dbl4 __attribute__((ext_vector_type(4)));
+
+__device__ __forceinline__ dbl4 mfma_k16(const dbl4 &a, const dbl4 &b, dbl4 c) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) c = __builtin_amdgcn_mfma_f64_16x16x4f64(a[q], b[q], c, 0, 0, 0);
+    return c;
+}
+
+// keeps a value's computation from being moved past this point
+__device__ __forceinline__ void pin(double &x) { asm volatile("" : "+v"(x)); }
+
+// f(0), f(1), .. f(N - 1) with compile-time arguments (register arrays are
+// indexed by constants from the start, whatever the unroller decides)
+template <int... I, typename F>
+__device__ __forceinline__ void static_for_seq(std::integer_sequence<int, I...>, F f) {
+    (f(std::integral_constant<int, I>{}), ...);
+}
+template <int N, typename F>
+__device__ __forceinline__ void static_for(F f) {
+    static_for_seq(std::make_integer_sequence<int, (N > 0 ? N : 0)>{}, f);
+}
+
+// orders one wavefront's LDS accesses (no instruction: LDS is in order)
+__device__ __forceinline__ void wave_lds_fence() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// x / s, correctly rounded, with y = 1 / s correctly rounded (Markstein: the
+// quotient's remainder is exact in one multiply-add, and adding remainder times
+// y rounds once)
+__device__ __forceinline__ double div_by(double x, double s, double y) {
+    const double q = x * y;
+    return __builtin_fma(__builtin_fma(-s, q, x), y, q);
+}
+
+// 1 / s for s = sqrt(d), correctly rounded: 1 / sqrt(d) from the hardware's
+// estimate to about an ulp beside the square root's own chain, then one
+// correction with s itself
+__device__ __forceinline__ double rcp_of_sqrt(double d, double s) {
+    double y = __builtin_amdgcn_rsq(d);
+    double e = __builtin_fma(-d * y, y, 1.0);
+    y = __builtin_fma(y, __builtin_fma(0.375 * e, e, 0.5 * e), y);
+    e = __builtin_fma(-s, y, 1.0);
+    return __builtin_fma(e, y, y);
+}
+
+// Cholesky elimination with 16 pivots by one wavefront, a row per lane: lanes
+// 0..15 hold the rows of a symmetric 16x16 block (both halves), the others
+// further rows of the same 16 columns.  On return a[j] of a lane is L(row, j)
+// (lanes r < 16: j < r), rounded as by the scalar loop l = a / sqrt(pivot),
+// a_rc -= l_r l_c; ds and dy of lane j < 16 hold sqrt(pivot j) and its
+// reciprocal.  bad: 1 + row0 + the first non-positive pivot (taken as 1), kept
+// if it is set already.  The lanes above the diagonal compute values nobody
+// reads.
+constexpr int EB = 16;
+__device__ __forceinline__ void elim16(double (&a)[EB], int lane, int row0, int &bad, double &ds, double &dy) {
+    asm volatile("" : "+v"(lane));   // (the lane masks are not to be kept across calls)
+    ds = dy = 1.0;
+    double s, y;
+    auto pivot = [&](double d, int j) {
+        const bool ok = d > 0.0;   // (uniform)
+        bad = !ok && bad == 0 ? 1 + row0 + j : bad;
+        d = ok ? d : 1.0;
+        s = sqrt(d);
+        y = rcp_of_sqrt(d, s);
+        if (lane == j) ds = s, dy = y;
+    };
+    pivot(lane_read(a[0], 0), 0);
+    static_for<EB>([&](auto jc) {
+        constexpr int j = decltype(jc)::value;
+        const double t = div_by(a[j], s, y);
+        a[j] = t;
+        if constexpr (j + 1 < EB) {
+            // the next pivot first: its chain runs beside the other columns
+            a[j + 1] = __builtin_fma(-lane_read(t, j + 1), t, a[j + 1]);
+            pivot(lane_read(a[j + 1], j + 1), j + 1);
+            // (at most four multipliers held in scalar registers at a time)
+            static_for<(EB - j + 1) / 4>([&](auto gc) {
+                constexpr int r = j + 2 + 4 * decltype(gc)::value;
+                double m[4] = {};
+                static_for<4>([&](auto u) { if constexpr (r + u < EB) m[u] = lane_read(t, r + u); });
+                static_for<4>([&](auto u) {
+                    if constexpr (r + u < EB) a[r + u] = __builtin_fma(-m[u], t, a[r + u]);
+                });
+                static_for<4>([&](auto u) { if constexpr (r + u < EB) pin(a[r + u]); });
+            });
+        }
+    });
+}
+
+// The rows below such a block: a row per lane, L(row, j) from the block's
+// columns and pivots in LDS (sT: column j at 16 j, 16-byte aligned; sd:
+// sqrt(pivot) and reciprocal).  The next column's values are read while one is
+// in use.
+__device__ __forceinline__ void subst16(double (&a)[EB], const double *sT, const double *sd) {
+    double m[2][EB], p[2][2];
+    auto column = [&](auto jc) __attribute__((always_inline)) {
+        constexpr int j = decltype(jc)::value, k = j & 1;
+        p[k][0] = sd[2 * j], p[k][1] = sd[2 * j + 1];
+        static_for<EB - 1 - j>([&](auto u) {
+            constexpr int r = j + 1 + decltype(u)::value;
+            m[k][r] = sT[EB * j + r];
+        });
+    };
+    column(std::integral_constant<int, 0>{});
+    static_for<EB>([&](auto jc) __attribute__((always_inline)) {
+        constexpr int j = decltype(jc)::value, k = j & 1;
+        if constexpr (j + 1 < EB) column(std::integral_constant<int, j + 1>{});
+        asm volatile("" ::: "memory");   // (no reads past the next column's)
+        const double t = div_by(a[j], p[k][0], p[k][1]);
+        a[j] = t;
+        static_for<EB - 1 - j>([&](auto u) {
+            constexpr int r = j + 1 + decltype(u)::value;
+            a[r] = __builtin_fma(-m[k][r], t, a[r]);
+        });
+        static_for<EB - 1 - j>([&](auto u) { pin(a[j + 1 + decltype(u)::value]); });
+    });
+}
+
 // Banded Cholesky A = L L^T of one symmetric positive definite matrix per
 // workgroup, in place in FP64.  Row-major band storage: row r holds columns
-// r-b .. r at band[r*(b+1) + (c - r + b)]; the diagonal slot holds 1/L_rr.  Blocked right-looking algorithm
-// with panels of NB columns: factor the diagonal block in LDS, solve the
-// rows below it (at most b of them), then update the (at most b x b) window
-// below the panel.  The fill of a banded Cholesky factor stays inside the
-// band.  status[i] = 1 + row of the first non-positive pivot.
-constexpr int CH_NB = 16;
-constexpr int CH_LD = CH_NB + 1;   // padded LDS row stride (bank spread)
+// r-b .. r at band[r*(b+1) + (c - r + b)]; the diagonal slot holds 1/L_rr.
+// The arithmetic is that of a right-looking loop over panels of 16 columns,
+// bit for bit: per earlier panel an entry loses one sum of 16 products formed
+// on its own in ascending order, then its own panel's elimination.  The order
+// of the work is left-looking, since each value is then written once
+// (right-looking rewrites the whole b x b window per panel), by panels of 32
+// columns (two of the 16), since the earlier columns are read once per panel,
+// and by blocks of 32 rows.  Per panel:
+//   (1) the diagonal block's sums, the earlier panels dealt to the wavefronts,
+//       and their ordered subtraction through LDS;
+//   (2) wavefront 0 eliminates that block (elim16, a row per lane) while each
+//       other wavefront forms one block below it, C = A - sums, by matrix
+//       instructions, transposed in registers;
+//   (3) the rows of C eliminated with the block's rows (subst16), then the
+//       blocks past the first ones, sums and elimination together.
+// Each wavefront brings its operands (32 panel rows and 32 block rows of 16
+// columns) in by whole 128-byte row segments, eight lanes to a row, and turns
+// them through LDS of its own, the next ones' loads in flight meanwhile:
+// operands loaded straight from the band (16 lanes on 16 rows) are bound by
+// the cache lines touched per load.  The fill of a banded Cholesky factor
+// stays inside the band; slots left of the band (the neighbouring row's) are
+// masked in the chunks that meet its edge.  Bound by the chain of one panel
+// (about 45,000 clocks at band 225: sums 15,000, the diagonal block's 32 pivots
+// 18,000 beside the first blocks' 33,000, elimination of the rows 12,000), one
+// workgroup per compute unit.  Against a right-looking loop with scalar
+// multiply-adds and window updates through memory: 512 matrices of 3,375 rows
+// and band 225 33.1 -> 7.1 ms, 27 of 3,000 and 335 22.5 -> 3.7 ms.  status[i] =
+// 1 + row of the first non-positive pivot.
+constexpr int DB = 32, DB_LD = DB + 1;   // panel width, padded LDS row stride (bank spread)
+constexpr int CH_ST = 64 * 16;           // a wavefront's chunk: 64 rows of 16 columns
+
+typedef double dbl2 __attribute__((ext_vector_type(2)));
+typedef double dbl2u __attribute__((ext_vector_type(2), aligned(8)));   // (rows start at any 8-byte address)
+
+// LDS place of column c of a chunk's row r: a lane's four operands (columns
+// g, g + 4, g + 8, g + 12) together, in 16-byte units permuted by the row, so
+// that eight rows' reads of one unit cover all banks
+__device__ __forceinline__ int chunk_unit(int r, int u) { return r * 16 + 2 * (u ^ (r & 7)); }
+__device__ __forceinline__ int chunk_at(int r, int c) {
+    return chunk_unit(r, 2 * (c & 3) + (c >> 3)) + ((c >> 2) & 1);
+}
+
+// this lane's operand of row r (columns j + g + 4 q); EDGE: columns below cmin
+// (left of the band) count as zero
+template <bool EDGE>
+__device__ __forceinline__ dbl4 chunk_operand(const double *st, int r, int lg, int j, int cmin) {
+    const dbl2 lo = *reinterpret_cast<const dbl2 *>(st + chunk_unit(r, 2 * lg));
+    const dbl2 hi = *reinterpret_cast<const dbl2 *>(st + chunk_unit(r, 2 * lg + 1));
+    dbl4 v = {lo[0], lo[1], hi[0], hi[1]};
+    if constexpr (EDGE) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) v[q] = j + lg + 4 * q >= cmin ? v[q] : 0.0;
+    }
+    return v;
+}
+
+// 32 rows of a chunk on their way to LDS: row 8 q + lane / 8, columns 2 (lane %
+// 8) + {0, 1} of the chunk at j, row q at p + d[q].  Slots left of the band
+// are read all the same: L(r, c) with c >= 0 lies at r b + b + c >= 0 of the
+// subdomain's array.
+__device__ __forceinline__ void chunk_load(dbl2 (&v)[4], const double *p, const int (&d)[4], int j) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) v[q] = *reinterpret_cast<const dbl2u *>(p + d[q] + j);
+}
+__device__ __forceinline__ void chunk_store(const dbl2 (&v)[4], double *st, int lane) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+        for (int h = 0; h < 2; ++h) st[chunk_at(8 * q + (lane >> 3), 2 * (lane & 7) + h)] = v[q][h];
+}
 
 template <int NT>
 __global__ __launch_bounds__(NT) void k_band_chol(double *__restrict__ band, const int64_t *__restrict__ off,
                                                   const int32_t *__restrict__ bwid,
                                                   const int64_t *__restrict__ rptr, int *__restrict__ status) {
-    extern __shared__ double smem[];
+    constexpr int NW = NT / 64;
+    static_assert(NW == 8 && DB * DB_LD <= 2 * CH_ST, "eight wavefronts; a block's rows fit a wavefront's chunks");
+    __shared__ __align__(16) double sC[NW][2 * CH_ST];   // the wavefronts' chunks
+    __shared__ double sX[DB * DB_LD];                    // the diagonal block, then its factor's rows
+    __shared__ __align__(16) double sd[2 * DB];          // sqrt(pivot) and reciprocal
+    __shared__ __align__(16) double sT[2][EB * EB];      // the factor's two 16x16 triangles by columns
     const int i = blockIdx.x;
     if (off[i + 1] == off[i]) return;   // no band (empty, or a supernodal subdomain)
     const int n = int(rptr[i + 1] - rptr[i]);
     const int b = bwid[i];
     const int64_t w = b + 1;
     double *L = band + off[i];
-    double *sD = smem;                 // CH_NB x CH_LD
-    double *sdg = sD + CH_NB * CH_LD;  // CH_NB
-    double *sP = sdg + CH_NB;          // b x CH_LD
-    const int tid = threadIdx.x;
-    for (int k0 = 0; k0 < n; k0 += CH_NB) {
-        const int kb = min(CH_NB, n - k0);
-        // (a) diagonal block, left-looking by columns
-        for (int e = tid; e < CH_NB * CH_NB; e += NT) {
-            const int t = e / CH_NB, s = e % CH_NB;
-            double v = 0.0;
-            if (t < kb && s <= t && t - s <= b) v = L[int64_t(k0 + t) * w + (s - t + b)];
-            sD[t * CH_LD + s] = v;
-        }
-        __syncthreads();
-        for (int j = 0; j < kb; ++j) {
-            const int t = j + tid;
-            if (t < kb) {
-                double v = sD[t * CH_LD + j];
-                for (int s = 0; s < j; ++s) v -= sD[t * CH_LD + s] * sD[j * CH_LD + s];
-                if (t == j) {
-                    if (!(v > 0.0)) {
-                        atomicCAS(status + i, 0, 1 + k0 + j);
-                        v = 1.0;
-                    }
-                    sdg[j] = sqrt(v);
-                } else {
-                    sD[t * CH_LD + j] = v;
-                }
-            }
-            __syncthreads();
-            if (t > j && t < kb) sD[t * CH_LD + j] /= sdg[j];
-            __syncthreads();
-        }
-        for (int e = tid; e < kb * kb; e += NT) {
-            const int t = e / kb, s = e % kb;
-            if (s <= t && t - s <= b)
-                L[int64_t(k0 + t) * w + (s - t + b)] = (s == t) ? 1.0 / sdg[t] : sD[t * CH_LD + s];
-        }
-        // (b) rows below the diagonal block: P <- P L_D^{-T}
-        const int rbeg = k0 + kb;
+    // (wv in a scalar register)
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    int li = lane & 15, lg = lane >> 4;
+    double *st = sC[wv];
+    // the block a wavefront forms in (2): the first block has the most columns
+    // and goes to the wavefront beside the diagonal block's (wavefronts wv and
+    // wv + 4 share a SIMD, whose matrix unit (2) leaves idle), the others pair
+    // a long one with a short one
+    const int t1 = wv < 4 ? wv + 1 : wv == 4 ? 1 : 12 - wv;
+    auto row_at = [&](int r) { return L + (int64_t(r) * w + (b - r)); };   // &L(r, 0)
+    // this lane's rows of a chunk of rows r0 .. r0 + 31 (past the matrix: its last row)
+    auto chunk_rows = [&](int r0, int (&d)[4]) {
+        const int r = min(r0 + (lane >> 3), n - 1);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) d[q] = (min(r0 + 8 * q + (lane >> 3), n - 1) - r) * b;
+        return row_at(r) + 2 * (lane & 7);
+    };
+    for (int k0 = 0; k0 < n; k0 += DB) {
+        const int kb = min(DB, n - k0);
         const int rend = min(n, k0 + kb + b);
-        const int m = max(0, rend - rbeg);
-        for (int q = tid; q < m; q += NT) {
-            const int r = rbeg + q;
-            const int s0 = max(0, r - b - k0);
-            double x[CH_NB];
+        const int nblk = (rend - k0 + DB - 1) / DB;
+        asm volatile("" : "+v"(li), "+v"(lg));   // (their addresses and masks are not to be kept across panels)
+        int dp[4];
+        const double *pp = chunk_rows(k0, dp);   // the panel's rows
+        // ---- (1) two earlier panels of 16 per wavefront and round: the lower
+        // tiles t of each sum at 768 slot + 256 t (value v of lane l at 64 v + l),
+        // then A - sums in panel order
+        const int j0 = max(0, k0 - b) & ~15;
+        for (int jr = j0; jr == j0 || jr < k0; jr += 32 * NW) {
+            const int c0 = min(k0 + li, n - 1) - b, c1 = min(k0 + 16 + li, n - 1) - b;
+            dbl2 v[2][4];
 #pragma unroll
-            for (int s = 0; s < CH_NB; ++s) {
-                double v = 0.0;
-                if (s >= s0 && s < kb) {
-                    v = L[int64_t(r) * w + (k0 + s - r + b)];
-                    for (int t = 0; t < s; ++t) v -= x[t] * sD[s * CH_LD + t];   // x[t] = 0 for t < s0
-                    v /= sdg[s];
+            for (int u = 0; u < 2; ++u) {
+                const int j = jr + 16 * (NW * u + wv);
+                if (j < k0) chunk_load(v[u], pp, dp, j);
+            }
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                const int j = jr + 16 * (NW * u + wv);
+                if (j < k0) {
+                    double *ck = st + 2 * 768;   // (past the sums)
+                    wave_lds_fence();
+                    chunk_store(v[u], ck, lane);
+                    wave_lds_fence();
+                    const dbl4 a0 = chunk_operand<true>(ck, li, lg, j, c0);
+                    const dbl4 a1 = chunk_operand<true>(ck, 16 + li, lg, j, c1);
+                    const dbl4 zero = {0.0, 0.0, 0.0, 0.0};
+                    const dbl4 s0 = mfma_k16(a0, a0, zero), s1 = mfma_k16(a1, a0, zero), s2 = mfma_k16(a1, a1, zero);
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        st[768 * u + 64 * q + lane] = s0[q];
+                        st[768 * u + 256 + 64 * q + lane] = s1[q];
+                        st[768 * u + 512 + 64 * q + lane] = s2[q];
+                    }
                 }
-                x[s] = v;
             }
+            __syncthreads();
+            const int np = min(2 * NW, (k0 - jr + 15) / 16);   // panels of this round
+            for (int e = threadIdx.x; e < 3 * 256; e += NT) {
+                const int t = e >> 8, q = (e >> 6) & 3, l = e & 63;
+                const int r = 16 * (t > 0) + (l >> 4) + 4 * q, c = 16 * (t > 1) + (l & 15);
+                double d;
+                if (jr == j0) {
+                    const int rr = min(k0 + r, n - 1);
+                    d = row_at(rr)[max(min(k0 + c, rr), rr - b)];
+                    d = r < kb && c <= r && r - c <= b ? d : (r >= kb && r == c ? 1.0 : 0.0);   // (identity past the matrix)
+                } else {
+                    d = sX[r * DB_LD + c];
+                }
+                if (r < kb && c <= r) {
+#pragma unroll 4
+                    for (int u = 0; u < np; ++u) d -= sC[u % NW][768 * (u / NW) + e];
+                }
+                if (c <= r) {   // (mirrored above the diagonal)
+                    sX[r * DB_LD + c] = d;
+                    sX[c * DB_LD + r] = d;
+                }
+            }
+            __syncthreads();
+        }
+        // ---- (2)
+        // C^T of block t (rows k0 + 32 t ..): cc[p][q], panel columns 16 p .., rows 16 q ..
+        dbl4 cc[2][2];
+        auto block_sum = [&](int t) __attribute__((always_inline)) {
+            const int r0 = k0 + DB * t;
+            int db[4];
+            const double *pb = chunk_rows(r0, db);
+            const int ib0 = min(r0 + li, n - 1), ib1 = min(r0 + 16 + li, n - 1);
+            int j = max(0, r0 - b) & ~15;
+            dbl2 va[4], vb[4];
+            if (j < k0) {
+                chunk_load(va, pp, dp, j);
+                chunk_load(vb, pb, db, j);
+            }
+            {
+                const double *rb0 = row_at(ib0) + k0, *rb1 = row_at(ib1) + k0;
+                const int m0 = ib0 - b - k0, m1 = ib1 - b - k0;
 #pragma unroll
-            for (int s = 0; s < CH_NB; ++s) {
-                sP[q * CH_LD + s] = x[s];
-                if (s >= s0 && s < kb) L[int64_t(r) * w + (k0 + s - r + b)] = x[s];
+                for (int p = 0; p < 2; ++p)
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) {
+                        const int c = 16 * p + lg + 4 * v;
+                        cc[p][0][v] = rb0[max(c, m0)];
+                        cc[p][1][v] = rb1[max(c, m1)];
+                    }
+#pragma unroll
+                for (int p = 0; p < 2; ++p)
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) {
+                        const int c = 16 * p + lg + 4 * v;
+                        cc[p][0][v] = c >= m0 ? cc[p][0][v] : 0.0;
+                        cc[p][1][v] = c >= m1 ? cc[p][1][v] : 0.0;
+                    }
             }
+            // one chunk in use, the next one in LDS, the one after loading
+            dbl4 f[4];
+            auto to_lds = [&](int buf) __attribute__((always_inline)) {
+                chunk_store(va, st + buf * CH_ST, lane);
+                chunk_store(vb, st + buf * CH_ST + CH_ST / 2, lane);
+            };
+            auto operands = [&](int buf, int jj, dbl4 (&g)[4]) __attribute__((always_inline)) {
+                const double *sb = st + buf * CH_ST;
+                // (uniform: does the chunk meet the band's left edge?)
+                if (jj < r0 + DB - 1 - b) {
+                    g[0] = chunk_operand<true>(sb, li, lg, jj, k0 + li - b);
+                    g[1] = chunk_operand<true>(sb, 16 + li, lg, jj, k0 + 16 + li - b);
+                    g[2] = chunk_operand<true>(sb, 32 + li, lg, jj, ib0 - b);
+                    g[3] = chunk_operand<true>(sb, 48 + li, lg, jj, ib1 - b);
+                } else {
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) g[u] = chunk_operand<false>(sb, 16 * u + li, lg, jj, 0);
+                }
+            };
+            auto load = [&](int jj) __attribute__((always_inline)) {
+                if (jj < k0) {
+                    chunk_load(va, pp, dp, jj);
+                    chunk_load(vb, pb, db, jj);
+                }
+            };
+            if (j < k0) {
+                to_lds(0);
+                load(j + 16);
+                for (int buf = 0; j < k0; j += 16, buf ^= 1) {
+                    wave_lds_fence();
+                    operands(buf, j, f);
+                    if (j + 16 < k0) {
+                        to_lds(buf ^ 1);
+                        load(j + 32);
+                    }
+#pragma unroll
+                    for (int p = 0; p < 2; ++p) {
+                        dbl4 s0 = {0.0, 0.0, 0.0, 0.0}, s1 = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) {
+                            s0 = __builtin_amdgcn_mfma_f64_16x16x4f64(f[p][q], f[2][q], s0, 0, 0, 0);
+                            s1 = __builtin_amdgcn_mfma_f64_16x16x4f64(f[p][q], f[3][q], s1, 0, 0, 0);
+                        }
+                        cc[p][0] -= s0;
+                        cc[p][1] -= s1;
+                    }
+                }
+                wave_lds_fence();
+            }
+        };
+        if (wv == 0) {
+            int r = lane & 31;
+            asm volatile("" : "+v"(r));   // (no addresses kept across panels)
+            double a[EB], ds, dy;
+            int bad = 0;
+            // columns 0..15: rows 0..15, and rows 16..31 in lanes 16..31
+            static_for<EB>([&](auto c) { a[c] = sX[r * DB_LD + c]; });
+            elim16(a, lane, 0, bad, ds, dy);
+            wave_lds_fence();
+            if (lane < 32) {
+                static_for<EB>([&](auto c) { sX[r * DB_LD + c] = a[c]; });
+                if (lane < EB) {
+                    static_for<EB>([&](auto c) { sT[0][EB * c + r] = a[c]; });
+                    sd[2 * lane] = ds, sd[2 * lane + 1] = dy;
+                }
+            }
+            wave_lds_fence();
+            // rows and columns 16..31 lose L10 L10^T
+            {
+                dbl4 f, s = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+                for (int q = 0; q < 4; ++q) f[q] = sX[(16 + li) * DB_LD + lg + 4 * q];
+                s = mfma_k16(f, f, s);
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    double *x = &sX[(16 + lg + 4 * v) * DB_LD + 16 + li];
+                    // (rows past the matrix keep the identity)
+                    if (max(lg + 4 * v, li) + 16 < kb) *x -= s[v];
+                }
+            }
+            wave_lds_fence();
+            static_for<EB>([&](auto c) { a[c] = sX[(16 + (r & 15)) * DB_LD + 16 + c]; });
+            elim16(a, lane, 16, bad, ds, dy);
+            wave_lds_fence();
+            if (lane < EB) {
+                static_for<EB>([&](auto c) {
+                    sX[(16 + r) * DB_LD + 16 + c] = a[c];
+                    sT[1][EB * c + r] = a[c];
+                });
+                sd[2 * (16 + lane)] = ds, sd[2 * (16 + lane) + 1] = dy;
+            }
+            if (bad && lane == 0) atomicCAS(status + i, 0, k0 + bad);
+        } else if (t1 < nblk) {
+            block_sum(t1);
         }
         __syncthreads();
-        // (c) trailing window: A(r, c) -= P(r,:) . P(c,:), c <= r
-        for (int e = tid; e < m * m; e += NT) {
-            const int rq = e / m, cq = e % m;
-            if (cq > rq) continue;
-            double acc = 0.0;
+        // ---- (3)
+        auto block_finish = [&](int t) __attribute__((always_inline)) {
+            const int r0 = k0 + DB * t;
+            // C by rows of 33 in this wavefront's chunks
+            wave_lds_fence();
 #pragma unroll
-            for (int s = 0; s < CH_NB; ++s) acc += sP[rq * CH_LD + s] * sP[cq * CH_LD + s];
-            const int r = rbeg + rq, c = rbeg + cq;
-            L[int64_t(r) * w + (c - r + b)] -= acc;
+            for (int p = 0; p < 2; ++p)
+#pragma unroll
+                for (int u = 0; u < 2; ++u)
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) st[(16 * u + li) * DB_LD + 16 * p + lg + 4 * v] = cc[p][u][v];
+            wave_lds_fence();
+            double *row = st + (lane & 31) * DB_LD;
+            double a[EB];
+            static_for<EB>([&](auto c) { a[c] = row[c]; });
+            subst16(a, sT[0], sd);
+            if (lane < 32) static_for<EB>([&](auto c) { row[c] = a[c]; });
+            wave_lds_fence();
+            // columns 16..31 lose L(rows, 0..15) L10^T
+            {
+                dbl4 x, f0, f1;
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    x[q] = sX[(16 + li) * DB_LD + lg + 4 * q];
+                    f0[q] = st[li * DB_LD + lg + 4 * q];
+                    f1[q] = st[(16 + li) * DB_LD + lg + 4 * q];
+                }
+                dbl4 s0 = {0.0, 0.0, 0.0, 0.0}, s1 = {0.0, 0.0, 0.0, 0.0};
+                s0 = mfma_k16(x, f0, s0);
+                s1 = mfma_k16(x, f1, s1);
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    st[li * DB_LD + 16 + lg + 4 * v] = cc[1][0][v] - s0[v];
+                    st[(16 + li) * DB_LD + 16 + lg + 4 * v] = cc[1][1][v] - s1[v];
+                }
+            }
+            wave_lds_fence();
+            static_for<EB>([&](auto c) { a[c] = row[16 + c]; });
+            subst16(a, sT[1], sd + 2 * EB);
+            wave_lds_fence();
+            if (lane < 32) static_for<EB>([&](auto c) { row[16 + c] = a[c]; });
+            wave_lds_fence();
+#pragma unroll 4
+            for (int q = 0; q < DB / 2; ++q) {
+                const int rr = 2 * q + (lane >> 5), c = lane & 31, r = r0 + rr;
+                if (r < rend && k0 + c >= r - b) row_at(r)[k0 + c] = st[rr * DB_LD + c];
+            }
+        };
+        if (wv == 0) {
+            for (int e = lane; e < kb * DB; e += 64) {
+                const int r = e / DB, c = e % DB;
+                const double v = r == c ? sd[2 * r + 1] : sX[r * DB_LD + c];
+                if (c <= r && r - c <= b) row_at(k0 + r)[k0 + c] = v;
+            }
+        } else if (t1 < nblk) {
+            block_finish(t1);
+        }
+#pragma unroll 1
+        for (int t = NW + wv; t < nblk; t += NW) {
+            block_sum(t);
+            block_finish(t);
         }
         __syncthreads();
     }
@@ -317,18 +715,42 @@ __global__ __launch_bounds__(NT) void k_band_chol(double *__restrict__ band, con
 // diagonal, 1/L_tt, is what the band already holds there), so that the
 // triangle solves of the block become products with X.  Only for bands of
 // at least BS_NB - 1, where the whole triangle lies inside the band.  One
-// 64-thread workgroup per diagonal block (block q of subdomain i with
-// blk_ptr[i] <= q < blk_ptr[i+1]); thread c forms column c of X by forward
-// substitution, X(t, c) = -(1/L_tt) sum_{c <= s < t} L(t, s) X(s, c).
+// wavefront per diagonal block (block q of subdomain i with blk_ptr[i] <= q <
+// blk_ptr[i+1]).  With L = [L0; M L1]: the inverses of the two 32x32 triangles
+// at once, a column per lane of either half, in registers (x_j = x_j / L_jj,
+// then x_r -= L(r, j) x_j for r > j: independent multiply-adds with broadcast
+// LDS reads), the sums M X0 by matrix instructions, then the lower left quarter
+// the same way from those sums.  Every value is the forward substitution's, bit
+// for bit: -(1/L_tt) sum_{c <= s < t} L(t, s) X(s, c) in ascending s.  (Both
+// triangles and the inverse in LDS, one value at a time per lane, held two
+// wavefronts per compute unit: 4.07 ms for 27,136 blocks; now 0.9 ms.)
 constexpr int BS_NB_INV = 64;
+
+// forward substitution with a 32x32 triangle (T: column j at LD j, reciprocal
+// diagonal), one right-hand side per lane
+template <int LD>
+__device__ __forceinline__ void subst_columns(double (&x)[DB], const double *T) {
+    static_for<DB>([&](auto jc) {
+        constexpr int j = decltype(jc)::value;
+        x[j] *= T[j * LD + j];
+        static_for<DB - 1 - j>([&](auto u) {
+            constexpr int r = j + 1 + decltype(u)::value;
+            x[r] = __builtin_fma(-T[j * LD + r], x[j], x[r]);
+        });
+        // (one column at a time: neither the LDS reads of later columns nor
+        // the multiply-adds of this one are to be moved past here)
+        static_for<DB - 1 - j>([&](auto u) { pin(x[j + 1 + decltype(u)::value]); });
+    });
+}
+
 __global__ __launch_bounds__(64) void k_band_invert_diag(double *__restrict__ band, const int64_t *__restrict__ off,
                                                          const int32_t *__restrict__ bwid,
                                                          const int64_t *__restrict__ rptr,
                                                          const int64_t *__restrict__ blk_ptr, int np) {
-    extern __shared__ double smem[];
-    constexpr int NB = BS_NB_INV, LD = NB + 1;
-    double *sT = smem;             // NB x LD: the block of L
-    double *sX = smem + NB * LD;   // NB x LD: its inverse
+    constexpr int NB = BS_NB_INV, LD = DB + 2;   // (even: 16-byte aligned columns)
+    // the triangles transposed (column j at j LD), M by rows, later M X0 by
+    // rows, X0 by rows
+    __shared__ __align__(16) double sT[2][DB * LD], sM[DB * LD], sX[DB * LD];
     const int64_t q = blockIdx.x;
     int lo = 0, hi = np;   // subdomain with blk_ptr[i] <= q < blk_ptr[i+1]
     while (hi - lo > 1) {
@@ -343,25 +765,61 @@ __global__ __launch_bounds__(64) void k_band_invert_diag(double *__restrict__ ba
     const int kb = min(NB, n - k0);
     const int64_t w = b + 1;
     double *L = band + off[i];
-    const int c = threadIdx.x;
-    for (int e = c; e < NB * NB; e += 64) {
-        const int t = e / NB, s2 = e % NB;
-        sT[t * LD + s2] = (t < kb && s2 <= t) ? L[int64_t(k0 + t) * w + (s2 - t + b)] : 0.0;
-    }
-    __syncthreads();
-    if (c < kb) {
-        sX[c * LD + c] = sT[c * LD + c];
-        for (int t = c + 1; t < kb; ++t) {
-            double acc = 0.0;
-            for (int s2 = c; s2 < t; ++s2) acc += sT[t * LD + s2] * sX[s2 * LD + c];
-            sX[t * LD + c] = -acc * sT[t * LD + t];
+    const int lane = threadIdx.x, half = lane >> 5, c = lane & 31, li = lane & 15, lg = lane >> 4;
+    // (rows past the last one: those of the identity)
+#pragma unroll 8
+    for (int t = 0; t < NB; ++t) {
+        const double v = t < kb && lane <= t ? L[int64_t(k0 + t) * w + (lane - t + b)] : (t == lane ? 1.0 : 0.0);
+        if (t < DB) {
+            if (half == 0) sT[0][c * LD + t] = v;
+        } else if (half == 0) {
+            sM[(t - DB) * LD + c] = v;
+        } else {
+            sT[1][c * LD + (t - DB)] = v;
         }
     }
     __syncthreads();
-    for (int e = c; e < NB * NB; e += 64) {
-        const int t = e / NB, s2 = e % NB;
-        if (t < kb && s2 < t) L[int64_t(k0 + t) * w + (s2 - t + b)] = sX[t * LD + s2];
+    double x[DB];
+    static_for<DB>([&](auto t) { x[t] = t == c ? 1.0 : 0.0; });
+    subst_columns<LD>(x, sT[half]);
+    static_for<DB>([&](auto t) {
+        if (half == 0) sX[t * LD + c] = x[t];
+        const int r = half * DB + t;
+        if (r < kb && c < t) L[int64_t(k0 + r) * w + (c - t + b)] = x[t];
+    });
+    if (kb <= DB) return;
+    __syncthreads();
+    // M X0: tiles of 16x16, ascending k (rows of X0 above its diagonal are zero)
+    dbl4 p[2][2] = {};
+#pragma unroll
+    for (int kt = 0; kt < 2; ++kt) {
+        dbl4 a[2], f[2];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int k = 16 * kt + 4 * u + lg;
+            a[0][u] = sM[li * LD + k];
+            a[1][u] = sM[(16 + li) * LD + k];
+            f[0][u] = sX[k * LD + li];
+            f[1][u] = sX[k * LD + 16 + li];
+        }
+#pragma unroll
+        for (int r = 0; r < 2; ++r)
+#pragma unroll
+            for (int s = 0; s < 2; ++s) p[r][s] = mfma_k16(a[r], f[s], p[r][s]);
     }
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < 2; ++r)
+#pragma unroll
+        for (int s = 0; s < 2; ++s)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) sM[(16 * r + lg + 4 * v) * LD + 16 * s + li] = p[r][s][v];
+    __syncthreads();
+    static_for<DB>([&](auto t) { x[t] = -sM[t * LD + c]; });
+    subst_columns<LD>(x, sT[1]);
+    static_for<DB>([&](auto t) {
+        if (half == 0 && DB + t < kb) L[int64_t(k0 + DB + t) * w + (c - DB - t + b)] = x[t];
+    });
 }
 
 // Casts a band (FP64) into the storage precision of the local factors.

@@ -1,0 +1,32 @@
+"""Numerical setup kernels at the edges of their tiles, through the applies
+they feed, against the FP64 oracle."""
+import numpy as np
+import pytest
+
+from oracle import gdsw_oracle as O
+from paper_2304_04876_amd import problems as P
+
+pytestmark = pytest.mark.gpu
+
+
+def _apply_matches(pr, tol=1e-12, Z=None, oracle_local="exact", coarse=None, **options):
+    """M^{-1} r to `tol` of the oracle's max-norm: FP64 factors of matrices
+    with condition numbers below 1e3 (1e-16 x 1e3, and a margin of 10)."""
+    import torch
+    from paper_2304_04876_amd import binding as B
+    g = B.Gdsw(pr.A, pr.part, pr.n_parts, pr.dpn, Z, **options)
+    M = O.GDSW(pr.A, pr.part, pr.dpn, pr.n_parts, Z=Z, local=oracle_local)
+    r = P.rhs_uniform(pr.n, 3)
+    z = torch.zeros(pr.n, dtype=torch.float64, device="cuda")
+    g.apply(torch.from_numpy(r).cuda(), z)
+    zr = M.apply(r)
+    g.close()
+    assert np.abs(z.cpu().numpy() - zr).max() <= tol * np.abs(zr).max()
+
+
+# one part: rows N^3 and band N^2 on both sides of the 16- and 32-wide panels
+# (8 rows, 27, 64 = two panels, 125, 216, 512 = whole blocks of 64); several:
+# interiors of every size down to one row, bands narrower than a panel
+@pytest.mark.parametrize("N,boxes", [(2, 1), (3, 1), (4, 1), (5, 1), (6, 1), (8, 1), (4, 2), (7, 3), (9, 2), (17, 2)])
+def test_band_cholesky(N, boxes):
+    _apply_matches(P.poisson3d(N, boxes))
