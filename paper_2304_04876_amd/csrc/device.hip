@@ -1011,9 +1011,20 @@ static void coarse_numeric(gdsw_handle_s *h, hipStream_t s) {
                                                   ST_BP_INT, s);
         const size_t lds2 = sizeof(double) * (size_t(std::max(S.max_nii, 1)) + BS_NB * BS_LD);
         if (lds2 > D.max_lds) throw DevError{GDSW_ERR_INVALID_ARG, "interior block too large for LDS"};
-        if (ikinds & 2)
-            hipLaunchKernelGGL((k_ext_solve<512, true>), dim3(S.np), dim3(512), lds2, s, iband, d_ioff, d_ibw,
-                               d_int_ptr, d_scol_ptr, d_ext_off, E, d_sub_blk, D.blk_val_off, D.phi);
+        if (ikinds & 2) {
+            // 16 right-hand sides at a time where the blocks in the widest
+            // band's reach fit LDS (bands up to 896)
+            int kmax = 0;
+            for (int i = 0; i < S.np; ++i) kmax = std::max<int>(kmax, int(S.scol_ptr[i + 1] - S.scol_ptr[i]));
+            const int nring = ext_mm_ring(S.max_ibw);
+            if (kmax > 0 && ext_mm_lds(nring) <= D.max_lds)
+                hipLaunchKernelGGL(k_ext_solve_mm, dim3(S.np, (kmax + XS_R - 1) / XS_R), dim3(256), ext_mm_lds(nring), s,
+                                   iband, d_ioff, d_ibw, d_int_ptr, d_scol_ptr, d_ext_off, E, d_sub_blk,
+                                   D.blk_val_off, D.phi, nring);
+            else
+                hipLaunchKernelGGL((k_ext_solve<512, true>), dim3(S.np), dim3(512), lds2, s, iband, d_ioff, d_ibw,
+                                   d_int_ptr, d_scol_ptr, d_ext_off, E, d_sub_blk, D.blk_val_off, D.phi);
+        }
         if (ikinds & 1)
             hipLaunchKernelGGL((k_ext_solve<512, false>), dim3(S.np), dim3(512), lds2, s, iband, d_ioff, d_ibw,
                                d_int_ptr, d_scol_ptr, d_ext_off, E, d_sub_blk, D.blk_val_off, D.phi);
@@ -1066,9 +1077,10 @@ static void coarse_numeric(gdsw_handle_s *h, hipStream_t s) {
             int64_t *d_t1off = D.setup_upload(S.t1_off, s);
             int kmax = 0;
             for (int i = 0; i < S.np; ++i) kmax = std::max<int>(kmax, int(S.scol_ptr[i + 1] - S.scol_ptr[i]));
-            dim3 grid(nblocks(int64_t(kmax) * kmax, 256), S.np);
-            hipLaunchKernelGGL(k_t1, grid, dim3(256), 0, s, d_int_ptr, d_scol_ptr, d_ext_off, E, d_sub_blk,
-                               D.blk_val_off, D.phi, d_t1off, T1);
+            const int tiles = (kmax + 15) / 16;
+            if (tiles > 0)
+                hipLaunchKernelGGL(k_t1, dim3(tiles * tiles, S.np), dim3(64), 0, s, d_int_ptr, d_scol_ptr, d_ext_off, E,
+                                   d_sub_blk, D.blk_val_off, D.phi, d_t1off, T1, tiles);
             int64_t *st = D.setup_upload(S.a0seg_tgt, s);
             int64_t *sp = D.setup_upload(S.a0seg_ptr, s);
             int64_t *ss = D.setup_upload(S.a0seg_src, s);

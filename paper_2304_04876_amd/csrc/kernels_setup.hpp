@@ -1319,7 +1319,8 @@ __global__ void k_ext_rhs(const double *__restrict__ Aval, const int64_t *__rest
 
 // Phi_{I_i} = -A_{I_i I_i}^{-1} E_i, one workgroup per subdomain, one right
 // hand side at a time through LDS, written into the subdomain's interior
-// block of Phi.
+// block of Phi: for bands without inverted diagonal blocks (interiors of a few
+// hundred rows) and for bands too wide for k_ext_solve_mm's LDS.
 template <int NT, bool INV>
 __global__ __launch_bounds__(1024) void k_ext_solve(const double *__restrict__ iband,
                                                   const int64_t *__restrict__ iband_off,
@@ -1352,24 +1353,244 @@ __global__ __launch_bounds__(1024) void k_ext_solve(const double *__restrict__ i
     }
 }
 
-// T1_i = E_i^T Phi_{I_i} (k_i x k_i), one thread per entry of one subdomain
-__global__ void k_t1(const int64_t *__restrict__ int_ptr, const int64_t *__restrict__ scol_ptr,
-                     const int64_t *__restrict__ ext_off, const double *__restrict__ E,
-                     const int32_t *__restrict__ sub_blk, const int64_t *__restrict__ blk_val_off,
-                     const double *__restrict__ phi, const int64_t *__restrict__ t1_off,
-                     double *__restrict__ T1) {
+// The same solve for 16 right-hand sides per workgroup (grid: subdomains x
+// groups of 16), for bands whose diagonal blocks are inverted: the band is
+// read once per pass for all 16 instead of once per right-hand side, and the
+// products are matrix instructions.  Blocks of 64 rows, 16 rows per wavefront,
+// right-hand sides transposed (D(i, j): right-hand side i, row j, so that a
+// column's rows are consecutive in memory).  Left-looking: a block takes the
+// contributions of the blocks before it (forward) or after it (backward) in
+// band_llt_solve's order, so that every value has that solve's bits: forward,
+// a row's 64 products per block are 16 chains of four (columns s, s + 16, s +
+// 32, s + 48: one matrix instruction each) added by the tree of row16_sum;
+// backward and in the triangles one ascending chain of 64.  The solved blocks
+// within reach are kept in LDS (a ring of nring = ceil(b / 64) + 1 blocks);
+// the forward pass turns its band rows (512-byte row segments) through LDS,
+// the backward pass reads operands in place (16 lanes on one row).  LDS:
+// ext_mm_lds(nring).  Against one right-hand side at a time: 24^3 elasticity
+// (27 interiors, 180 right-hand sides) 52.7 -> 0.50 ms, 128^3 Poisson (512
+// interiors of 3,375 rows, 6 right-hand sides padded to 16; bound by reading
+// the band twice) 9.0 -> 2.07 ms.
+constexpr int XS_R = 16;   // right-hand sides per workgroup
+__host__ __device__ constexpr int ext_mm_ring(int b) { return (b + BS_NB - 1) / BS_NB + 1; }
+__host__ __device__ constexpr size_t ext_mm_lds(int nring) {
+    return sizeof(double) * (size_t(nring) + 1 + 4) * (XS_R * BS_NB);
+}
+
+__global__ __launch_bounds__(256) void k_ext_solve_mm(const double *__restrict__ iband,
+                                                      const int64_t *__restrict__ iband_off,
+                                                      const int32_t *__restrict__ ibw,
+                                                      const int64_t *__restrict__ int_ptr,
+                                                      const int64_t *__restrict__ scol_ptr,
+                                                      const int64_t *__restrict__ ext_off,
+                                                      const double *__restrict__ E,
+                                                      const int32_t *__restrict__ sub_blk,
+                                                      const int64_t *__restrict__ blk_val_off,
+                                                      double *__restrict__ phi, int nring) {
+    extern __shared__ __align__(16) double sxs[];
+    const int i = blockIdx.x, c0 = XS_R * blockIdx.y;
+    const int n = int(int_ptr[i + 1] - int_ptr[i]);
+    const int k = int(scol_ptr[i + 1] - scol_ptr[i]);
+    const int g = sub_blk[i], b = ibw[i];
+    if (n == 0 || k <= c0 || g < 0 || !band_inverted(b)) return;
+    constexpr int BLK = XS_R * BS_NB;
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int li = lane & 15, lg = lane >> 4;
+    double *ring = sxs;                  // solved blocks, right-hand side i, row s at 64 i + (s ^ i)
+    double *sR = sxs + nring * BLK;      // the block's right-hand sides before its triangle
+    double *st = sR + BLK + wv * BLK;    // this wavefront's band rows, in 16-byte units permuted by the row
+    const int64_t w = b + 1;
+    const double *L = iband + iband_off[i];
+    auto row_at = [&](int r) { return L + (int64_t(r) * w + (b - r)); };   // &L(r, 0)
+    const int nblk = (n + BS_NB - 1) / BS_NB;
+    const double *Ei = E + ext_off[i] + int64_t(c0) * n;
+    double *X = phi + blk_val_off[g] + int64_t(c0) * n;
+    const int nc = min(XS_R, k - c0);
+    // band rows r0 .. r0 + 15, columns k0 .. k0 + 63: two rows per load, 32
+    // lanes to a row (rows past the matrix: its last one; slots left of the
+    // band are read, L(r, c) with c >= 0 lies at r b + b + c >= 0; columns
+    // right of the diagonal, in a block's own triangle, at most up to the
+    // array's last value)
+    const int64_t last = int64_t(n) * w - 1;
+    dbl2 v[8];
+    auto load_rows = [&](int r0, int k0) __attribute__((always_inline)) {
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+            const int r = min(r0 + 2 * q + (lane >> 5), n - 1);
+            const int64_t at = int64_t(r) * b + b + k0 + 2 * (lane & 31);
+            if (k0 + BS_NB <= r0)
+                v[q] = *reinterpret_cast<const dbl2u *>(L + at);
+            else
+                v[q] = dbl2{L[min(at, last)], L[min(at + 1, last)]};
+        }
+    };
+    auto rows_to_lds = [&]() __attribute__((always_inline)) {
+        wave_lds_fence();
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+            const int r = 2 * q + (lane >> 5);
+            *reinterpret_cast<dbl2 *>(st + r * BS_NB + 2 * ((lane & 31) ^ (r & 7))) = v[q];
+        }
+        wave_lds_fence();
+    };
+    // ---- forward
+    for (int blk = 0; blk < nblk; ++blk) {
+        const int r0 = blk * BS_NB + 16 * wv, r = r0 + li, rr = min(r, n - 1);
+        dbl4 y;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int s = lg + 4 * u;
+            y[u] = s < nc && r < n ? Ei[int64_t(s) * n + r] : 0.0;
+        }
+        const int kf = max(0, r0 - b) / BS_NB;   // (earlier blocks are out of the band's reach)
+        load_rows(r0, (kf < blk ? kf : blk) * BS_NB);
+        for (int kk = kf; kk < blk; ++kk) {
+            const int k0 = kk * BS_NB;
+            rows_to_lds();
+            load_rows(r0, k0 + BS_NB);   // (the next block's, at last the triangle's)
+            const double *yk = ring + (kk % nring) * BLK + li * BS_NB;
+            const int cmin = rr - b - k0 - 16 * lg;
+            // chains s and s + 1 of the tree's leaves, pairs, quads, ...
+            dbl4 q4[4];
+#pragma unroll
+            for (int m = 0; m < 4; ++m) {
+                dbl4 p[4];
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    const int s = 4 * m + 2 * h;
+                    const dbl2 f = *reinterpret_cast<const dbl2 *>(st + li * BS_NB + 2 * ((8 * lg + s / 2) ^ (li & 7)));
+#pragma unroll
+                    for (int u = 0; u < 2; ++u) {
+                        const dbl4 zero = {0.0, 0.0, 0.0, 0.0};
+                        p[2 * h + u] = __builtin_amdgcn_mfma_f64_16x16x4f64(
+                            yk[(16 * lg + s + u) ^ li], s + u >= cmin ? f[u] : 0.0, zero, 0, 0, 0);
+                    }
+                }
+                q4[m] = (p[0] + p[1]) + (p[2] + p[3]);
+            }
+            y -= (q4[0] + q4[1]) + (q4[2] + q4[3]);
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int s = lg + 4 * u;
+            sR[s * BS_NB + ((16 * wv + li) ^ s)] = y[u];
+        }
+        rows_to_lds();
+        __syncthreads();
+        // the triangle: rows 16 wv + li of the inverse, columns up to the row
+        y = dbl4{0.0, 0.0, 0.0, 0.0};
+        for (int q = 0; q < 4 * (wv + 1); ++q) {
+            const int s = 4 * q + lg;
+            const double f = st[li * BS_NB + 2 * ((s >> 1) ^ (li & 7)) + (s & 1)];
+            y = __builtin_amdgcn_mfma_f64_16x16x4f64(sR[li * BS_NB + (s ^ li)], s <= 16 * wv + li ? f : 0.0, y, 0, 0, 0);
+        }
+        double *yb = ring + (blk % nring) * BLK;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int s = lg + 4 * u;
+            if (r >= n) y[u] = 0.0;
+            yb[s * BS_NB + ((16 * wv + li) ^ s)] = y[u];
+            if (s < nc && r < n) X[int64_t(s) * n + r] = y[u];
+        }
+        __syncthreads();
+    }
+    // ---- backward (a lane reads back the values it wrote)
+    for (int blk = nblk - 1; blk >= 0; --blk) {
+        const int c = blk * BS_NB + 16 * wv + li;   // the column (c < n where it is stored)
+        const int cc = min(c, n - 1);
+        dbl4 y;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int s = lg + 4 * u;
+            y[u] = s < nc && c < n ? X[int64_t(s) * n + c] : 0.0;
+        }
+        const int kl = min(nblk - 1, (blk * BS_NB + 16 * wv + 15 + b) / BS_NB);
+        for (int kk = kl; kk > blk; --kk) {
+            const int k0 = kk * BS_NB;
+            const double *zk = ring + (kk % nring) * BLK + li * BS_NB;
+            double f[16];
+#pragma unroll
+            for (int q = 0; q < 16; ++q) {
+                const int r = min(k0 + 4 * q + lg, n - 1);
+                f[q] = row_at(r)[cc];
+            }
+            dbl4 a = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+            for (int q = 0; q < 16; ++q) {
+                const int r = k0 + 4 * q + lg;
+                a = __builtin_amdgcn_mfma_f64_16x16x4f64(zk[(4 * q + lg) ^ li], r < n && c >= r - b ? f[q] : 0.0, a, 0, 0, 0);
+            }
+            y -= a;
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int s = lg + 4 * u;
+            sR[s * BS_NB + ((16 * wv + li) ^ s)] = y[u];
+        }
+        __syncthreads();
+        y = dbl4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll 4
+        for (int q = 4 * wv; q < 16; ++q) {
+            const int s = 4 * q + lg, r = blk * BS_NB + s;
+            const double f = r < n && s >= 16 * wv + li ? row_at(min(r, n - 1))[min(c, min(r, n - 1))] : 0.0;
+            y = __builtin_amdgcn_mfma_f64_16x16x4f64(sR[li * BS_NB + (s ^ li)], f, y, 0, 0, 0);
+        }
+        double *zb = ring + (blk % nring) * BLK;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int s = lg + 4 * u;
+            if (c >= n) y[u] = 0.0;
+            zb[s * BS_NB + ((16 * wv + li) ^ s)] = y[u];
+            if (s < nc && c < n) X[int64_t(s) * n + c] = -y[u];
+        }
+        __syncthreads();
+    }
+}
+
+// T1_i = E_i^T Phi_{I_i} (k_i x k_i), one wavefront per 16x16 tile of one
+// subdomain, the rows of I_i in ascending order through matrix instructions
+// (each value is one ascending chain over the rows; 128^3 Poisson 0.88 -> 0.18 ms
+// and 24^3 elasticity 1.52 -> 0.09 ms against a thread per value).  Four
+// instructions' operands are loaded at a time, the next four's beside them.
+__global__ __launch_bounds__(64) void k_t1(const int64_t *__restrict__ int_ptr, const int64_t *__restrict__ scol_ptr,
+                                           const int64_t *__restrict__ ext_off, const double *__restrict__ E,
+                                           const int32_t *__restrict__ sub_blk,
+                                           const int64_t *__restrict__ blk_val_off, const double *__restrict__ phi,
+                                           const int64_t *__restrict__ t1_off, double *__restrict__ T1, int tiles) {
     const int i = blockIdx.y;
     const int n = int(int_ptr[i + 1] - int_ptr[i]);
     const int k = int(scol_ptr[i + 1] - scol_ptr[i]);
     const int g = sub_blk[i];
-    const int e = blockIdx.x * blockDim.x + threadIdx.x;
-    if (n == 0 || k == 0 || g < 0 || e >= k * k) return;
-    const int a = e / k, bcol = e % k;
-    const double *Ea = E + ext_off[i] + int64_t(a) * n;
-    const double *Xb = phi + blk_val_off[g] + int64_t(bcol) * n;
-    double acc = 0.0;
-    for (int l = 0; l < n; ++l) acc += Ea[l] * Xb[l];
-    T1[t1_off[i] + e] = acc;
+    const int ta = 16 * (blockIdx.x / tiles), tb = 16 * (blockIdx.x % tiles);
+    if (n == 0 || ta >= k || tb >= k || g < 0) return;
+    const int lane = threadIdx.x, li = lane & 15, lg = lane >> 4;
+    const double *Ea = E + ext_off[i] + int64_t(min(ta + li, k - 1)) * n;
+    const double *Xb = phi + blk_val_off[g] + int64_t(min(tb + li, k - 1)) * n;
+    constexpr int U = 4;
+    dbl4 acc = {0.0, 0.0, 0.0, 0.0};
+    double a[U], x[U];
+    auto load = [&](int l0, double (&aa)[U], double (&xx)[U]) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int l = l0 + 4 * u + lg;
+            aa[u] = Ea[min(l, n - 1)];
+            xx[u] = l < n ? Xb[l] : 0.0;   // (rows past the last add nothing)
+        }
+    };
+    load(0, a, x);
+    for (int l0 = 0; l0 < n; l0 += 4 * U) {
+        double a2[U], x2[U];
+        load(l0 + 4 * U, a2, x2);
+#pragma unroll
+        for (int u = 0; u < U; ++u) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a[u], x[u], acc, 0, 0, 0);
+#pragma unroll
+        for (int u = 0; u < U; ++u) a[u] = a2[u], x[u] = x2[u];
+    }
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+        const int ra = ta + lg + 4 * v, cb = tb + li;
+        if (ra < k && cb < k) T1[t1_off[i] + int64_t(ra) * k + cb] = acc[v];
+    }
 }
 
 // Interface-interface part of A_0: for every component pair (c, d) with
