@@ -317,7 +317,7 @@ struct Device {
 // Scratch tags of the numerical setup (Device::setup_scratch).
 enum SetupTag {
     ST_STATUS = 1, ST_LVAL, ST_FI_A, ST_FI_V, ST_BAND64, ST_BP_LOCAL, ST_BP_INT, ST_E, ST_IBAND, ST_T2, ST_T1,
-    ST_GJ_P, ST_GJ_W, ST_SUB_BLK, ST_ND64
+    ST_GJ_P, ST_GJ_W, ST_SUB_BLK, ST_ND64, ST_GJ_K
 };
 
 // Values of A in the sliced ELL layout of the Krylov SpMV (slices of SELL_C
@@ -1106,17 +1106,19 @@ static void coarse_numeric(gdsw_handle_s *h, hipStream_t s) {
         for (int k = 0; k < S.nprob; ++k) nmax = std::max(nmax, S.prob_c0[k + 1] - S.prob_c0[k]);
         double *P = D.setup_scratch<double>(ST_GJ_P, GJ_NB * GJ_NB);
         double *W = D.setup_scratch<double>(ST_GJ_W, int64_t(nmax) * GJ_NB);
+        // the rows A(K, :): in E's place (used up by now) where they fit it
+        const int64_t nkr = int64_t(nmax) * GJ_NB;
+        double *Kr = next >= nkr ? E : D.setup_scratch<double>(ST_GJ_K, nkr);
         HIPCHK(hipMemsetAsync(d_status, 0, sizeof(int) * S.np, s));
         for (int k = 0; k < S.nprob; ++k) {
             const int nk = S.prob_c0[k + 1] - S.prob_c0[k];
             double *Ak = D.A0inv + S.a0_off[k];
-            const dim3 tiles((nk + 63) / 64, (nk + 63) / 64);
+            const int nt = (nk + 63) / 64;
             for (int k0 = 0; k0 < nk; k0 += GJ_NB) {
                 const int kb = std::min(GJ_NB, nk - k0);
-                hipLaunchKernelGGL(k_gj_pivot, dim3(1), dim3(256), 0, s, Ak, nk, k0, kb, P, d_status + (k % S.np));
-                hipLaunchKernelGGL(k_gj_panel, dim3(nblocks(nk, 256)), dim3(256), 0, s, Ak, nk, k0, kb, P, W);
-                hipLaunchKernelGGL(k_gj_update, tiles, dim3(256), 0, s, Ak, nk, k0, kb, W);
-                hipLaunchKernelGGL(k_gj_fix, dim3(nblocks(nk, 256)), dim3(256), 0, s, Ak, nk, k0, kb, W, P);
+                hipLaunchKernelGGL(k_gj_panel, dim3(nt), dim3(256), 0, s, Ak, nk, k0, kb, P, W, Kr, int64_t(nmax),
+                                   d_status + (k % S.np));
+                hipLaunchKernelGGL(k_gj_update, dim3(nt, nt), dim3(256), 0, s, Ak, nk, k0, kb, W, Kr, int64_t(nmax), P);
             }
         }
         hipLaunchKernelGGL(k_negate, dim3(nblocks(na0, 256, 65536)), dim3(256), 0, s, D.A0inv, na0);
@@ -1124,6 +1126,7 @@ static void coarse_numeric(gdsw_handle_s *h, hipStream_t s) {
         check_status(D, d_status, std::min(S.np, S.nprob), s, "coarse matrix inverse");
         D.setup_release(P, 8 * GJ_NB * GJ_NB);
         D.setup_release(W, 8 * size_t(nmax) * GJ_NB);
+        if (Kr != E) D.setup_release(Kr, 8 * size_t(nkr));
     }
     if (D.phi32) {
         hipLaunchKernelGGL(k_cast<float>, dim3(nblocks(nphi, 256, 65536)), dim3(256), 0, s, D.phi, D.phi32, nphi);

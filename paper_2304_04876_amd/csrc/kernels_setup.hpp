@@ -1654,123 +1654,143 @@ __global__ void k_symmetrize(const double *__restrict__ A, double *__restrict__ 
 constexpr int GJ_NB = 32;
 constexpr int GJ_LD = GJ_NB + 1;
 
-// P = A_KK^{-1} in LDS by scalar sweeps, written to Pout (kb x kb)
-__global__ __launch_bounds__(256) void k_gj_pivot(const double *__restrict__ A, int n, int k0, int kb,
-                                                  double *__restrict__ Pout, int *__restrict__ status) {
-    __shared__ double S[GJ_NB * GJ_LD];
-    const int tid = threadIdx.x;
-    for (int e = tid; e < kb * kb; e += 256) {
-        const int r = e / kb, c = e % kb;
-        S[r * GJ_LD + c] = A[int64_t(k0 + r) * n + (k0 + c)];
+// Two launches per block K (a separate pivot kernel of one workgroup and
+// separate kernels for W and for storing it took 56, 48 and 16 us per block at
+// n = 2,863 beside the update's 48; now 23 + 31 us).
+
+// P = A_KK^{-1} by scalar sweeps, in every workgroup (one launch less, and no
+// workgroup waits for another's), then for 64 rows i per workgroup: W(i, :) =
+// A(i, K) P (rows in K get 0) and Kr(:, i) = A(K, i) as the update needs
+// them, and the block's new values A(i, K) = W(i, :), A(K, i) = W(i, :)^T for i
+// outside K.  A_KK itself is left for the update to replace (other workgroups
+// read it here).  Each sweep writes the other of two LDS copies, one barrier per
+// pivot; W is one ascending chain of products per value, by matrix instructions.
+__global__ __launch_bounds__(256) void k_gj_panel(double *__restrict__ A, int n, int k0, int kb,
+                                                  double *__restrict__ Pout, double *__restrict__ W,
+                                                  double *__restrict__ Kr, int64_t ldk, int *__restrict__ status) {
+    __shared__ double S[2][GJ_NB * GJ_LD];
+    __shared__ double sW[64 * GJ_LD];
+    const int tid = threadIdx.x, i0 = blockIdx.x * 64;
+    const int pr = tid >> 5, pc = tid & 31;   // this thread's values (pr + 8 q, pc)
+    const int wv = tid >> 6, lane = tid & 63, li = lane & 15, lg = lane >> 4;
+    // A(i, K) of this wavefront's 16 rows as operands, A(K, i) of the 64 columns
+    const int ir = min(i0 + 16 * wv + li, n - 1);
+    double a[8], kr[8];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+        const int t = 4 * q + lg;
+        a[q] = t < kb ? A[int64_t(ir) * n + k0 + t] : 0.0;
+        kr[q] = A[int64_t(k0 + min(wv + 4 * q, kb - 1)) * n + min(i0 + lane, n - 1)];
+    }
+    double v[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const int r = pr + 8 * q;
+        v[q] = r < kb && pc < kb ? A[int64_t(k0 + r) * n + (k0 + pc)] : 0.0;
+        S[0][r * GJ_LD + pc] = v[q];
     }
     __syncthreads();
     for (int j = 0; j < kb; ++j) {
-        const double piv = S[j * GJ_LD + j];
+        const double *T = S[j & 1];
+        const double piv = T[j * GJ_LD + j];
         if (!(piv > 0.0)) {
             if (tid == 0) atomicCAS(status, 0, 1 + k0 + j);
             return;
         }
-        const double p = 1.0 / piv;
-        // all new values are computed from the old ones before any is stored
-        double upd[4];
-        int cnt = 0;
-        for (int e = tid; e < kb * kb; e += 256, ++cnt) {
-            const int rr = e / kb, cc = e % kb;
-            double v = S[rr * GJ_LD + cc];
-            const double aij = S[rr * GJ_LD + j], ajk = S[j * GJ_LD + cc];
-            if (rr == j && cc == j) v = -p;
-            else if (cc == j) v = aij * p;
-            else if (rr == j) v = p * ajk;
-            else v = v - aij * p * ajk;
-            upd[cnt] = v;
+        const double p = 1.0 / piv, ajk = T[j * GJ_LD + pc];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int r = pr + 8 * q;
+            const double aij = T[r * GJ_LD + j];
+            if (r == j && pc == j) v[q] = -p;
+            else if (pc == j) v[q] = aij * p;
+            else if (r == j) v[q] = p * ajk;
+            else v[q] = v[q] - aij * p * ajk;
+            S[(j & 1) ^ 1][r * GJ_LD + pc] = v[q];
         }
         __syncthreads();
-        cnt = 0;
-        for (int e = tid; e < kb * kb; e += 256, ++cnt) S[(e / kb) * GJ_LD + (e % kb)] = upd[cnt];
-        __syncthreads();
     }
-    for (int e = tid; e < kb * kb; e += 256) Pout[e] = -S[(e / kb) * GJ_LD + (e % kb)];
-}
-
-// W(i, :) = A(i, K) P for every row i (rows in K get 0)
-__global__ void k_gj_panel(const double *__restrict__ A, int n, int k0, int kb, const double *__restrict__ P,
-                           double *__restrict__ W) {
-    __shared__ double sP[GJ_NB * GJ_NB];
-    for (int e = threadIdx.x; e < kb * kb; e += blockDim.x) sP[e] = P[e];
+    const double *T = S[kb & 1];   // -P
+    if (blockIdx.x == 0)
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            if (pr + 8 * q < kb && pc < kb) Pout[(pr + 8 * q) * kb + pc] = -v[q];
+    // W, 16 rows per wavefront
+    dbl4 w0 = {0.0, 0.0, 0.0, 0.0}, w1 = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+        const int t = 4 * q + lg;   // (rows of P past kb: zeros, a is zero there too)
+        w0 = __builtin_amdgcn_mfma_f64_16x16x4f64(a[q], t < kb ? -T[t * GJ_LD + li] : 0.0, w0, 0, 0, 0);
+        w1 = __builtin_amdgcn_mfma_f64_16x16x4f64(a[q], t < kb ? -T[t * GJ_LD + 16 + li] : 0.0, w1, 0, 0, 0);
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+        const int r = 16 * wv + lg + 4 * u, i = i0 + r;
+        const bool inK = i >= k0 && i < k0 + kb;
+        sW[r * GJ_LD + li] = inK || li >= kb ? 0.0 : w0[u];
+        sW[r * GJ_LD + 16 + li] = inK || 16 + li >= kb ? 0.0 : w1[u];
+    }
     __syncthreads();
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    double a[GJ_NB];
 #pragma unroll
-    for (int t = 0; t < GJ_NB; ++t) a[t] = (t < kb) ? A[int64_t(i) * n + k0 + t] : 0.0;
-    const bool inK = (i >= k0 && i < k0 + kb);
-    for (int s = 0; s < kb; ++s) {
-        double acc = 0.0;
+    for (int q = 0; q < 8; ++q) {   // rows of W: two per pass and wavefront
+        const int r = 2 * (wv + 4 * q) + (lane >> 5), t = lane & 31, i = i0 + r;
+        if (i >= n) continue;
+        const double x = sW[r * GJ_LD + t];
+        W[int64_t(i) * GJ_NB + t] = x;
+        if (t < kb && !(i >= k0 && i < k0 + kb)) A[int64_t(i) * n + k0 + t] = x;
+    }
+    const int i = i0 + lane;
+    if (i < n) {
+        const bool inK = i >= k0 && i < k0 + kb;
 #pragma unroll
-        for (int t = 0; t < GJ_NB; ++t)
-            if (t < kb) acc += a[t] * sP[t * kb + s];
-        W[int64_t(i) * GJ_NB + s] = inK ? 0.0 : acc;
+        for (int q = 0; q < 8; ++q) {
+            const int t = wv + 4 * q;
+            if (t < kb) {
+                Kr[t * ldk + i] = kr[q];
+                if (!inK) A[int64_t(k0 + t) * n + i] = sW[lane * GJ_LD + t];
+            }
+        }
     }
 }
 
-// A(i, j) -= W(i, :) . A(K, j) for i, j outside K; 64x64 tiles, 4x4 per thread
+// A(i, j) -= W(i, :) . Kr(:, j) for i, j outside K, A_KK = -P; 64x64 tiles, 16
+// rows per wavefront, by matrix instructions (one ascending chain per value,
+// subtracted once).  Bound by reading and writing A.
 __global__ __launch_bounds__(256) void k_gj_update(double *__restrict__ A, int n, int k0, int kb,
-                                                   const double *__restrict__ W) {
-    __shared__ double sW[64 * GJ_LD];
-    __shared__ double sK[GJ_NB * 65];
-    const int i0 = blockIdx.y * 64, j0 = blockIdx.x * 64;
-    const int tid = threadIdx.x;
-    for (int e = tid; e < 64 * GJ_NB; e += 256) {
-        const int r = e / GJ_NB, t = e % GJ_NB;
-        const int i = i0 + r;
-        sW[r * GJ_LD + t] = (i < n && t < kb) ? W[int64_t(i) * GJ_NB + t] : 0.0;
-    }
-    for (int e = tid; e < GJ_NB * 64; e += 256) {
-        const int t = e / 64, c = e % 64;
-        const int j = j0 + c;
-        sK[t * 65 + c] = (j < n && t < kb) ? A[int64_t(k0 + t) * n + j] : 0.0;
-    }
-    __syncthreads();
-    const int tr = (tid / 16) * 4, tc = (tid % 16) * 4;
-    double acc[4][4] = {};
-    for (int t = 0; t < kb; ++t) {
-        double wv[4], kv[4];
+                                                   const double *__restrict__ W, const double *__restrict__ Kr,
+                                                   int64_t ldk, const double *__restrict__ P) {
+    const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63, li = lane & 15, lg = lane >> 4;
+    const int i0 = blockIdx.y * 64 + 16 * wv, j0 = blockIdx.x * 64;
+    const int ir = min(i0 + li, n - 1);
+    double old[4][4];
 #pragma unroll
-        for (int a = 0; a < 4; ++a) wv[a] = sW[(tr + a) * GJ_LD + t];
+    for (int u = 0; u < 4; ++u)
 #pragma unroll
-        for (int c = 0; c < 4; ++c) kv[c] = sK[t * 65 + tc + c];
+        for (int v = 0; v < 4; ++v)
+            old[u][v] = A[int64_t(min(i0 + lg + 4 * v, n - 1)) * n + min(j0 + 16 * u + li, n - 1)];
+    dbl4 acc[4] = {};
 #pragma unroll
-        for (int a = 0; a < 4; ++a)
+    for (int q = 0; q < 8; ++q) {
+        const int t = 4 * q + lg;
+        const double a = W[int64_t(ir) * GJ_NB + t];   // (zero past kb)
+        const int64_t row = min(t, kb - 1) * ldk;
 #pragma unroll
-            for (int c = 0; c < 4; ++c) acc[a][c] += wv[a] * kv[c];
+        for (int u = 0; u < 4; ++u)
+            acc[u] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, Kr[row + min(j0 + 16 * u + li, n - 1)], acc[u], 0, 0, 0);
     }
 #pragma unroll
-    for (int a = 0; a < 4; ++a) {
-        const int i = i0 + tr + a;
-        if (i >= n || (i >= k0 && i < k0 + kb)) continue;
+    for (int v = 0; v < 4; ++v) {
+        const int i = i0 + lg + 4 * v;
+        if (i >= n) continue;
+        const bool iK = i >= k0 && i < k0 + kb;
 #pragma unroll
-        for (int c = 0; c < 4; ++c) {
-            const int j = j0 + tc + c;
-            if (j >= n || (j >= k0 && j < k0 + kb)) continue;
-            A[int64_t(i) * n + j] -= acc[a][c];
+        for (int u = 0; u < 4; ++u) {
+            const int j = j0 + 16 * u + li;
+            if (j >= n) continue;
+            const bool jK = j >= k0 && j < k0 + kb;
+            if (iK && jK) A[int64_t(i) * n + j] = -P[(i - k0) * kb + (j - k0)];
+            else if (!iK && !jK) A[int64_t(i) * n + j] = old[u][v] - acc[u][v];
         }
-    }
-}
-
-// A(i, K) = W(i, :), A(K, i) = W(i, :)^T (i outside K), A_KK = -P
-__global__ void k_gj_fix(double *__restrict__ A, int n, int k0, int kb, const double *__restrict__ W,
-                         const double *__restrict__ P) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    if (i >= k0 && i < k0 + kb) {
-        const int r = i - k0;
-        for (int t = 0; t < kb; ++t) A[int64_t(i) * n + k0 + t] = -P[r * kb + t];
-        return;
-    }
-    for (int t = 0; t < kb; ++t) {
-        const double v = W[int64_t(i) * GJ_NB + t];
-        A[int64_t(i) * n + k0 + t] = v;
-        A[int64_t(k0 + t) * n + i] = v;
     }
 }
 
