@@ -1053,8 +1053,10 @@ static void coarse_numeric(gdsw_handle_s *h, hipStream_t s) {
             int32_t *pld = D.setup_upload(S.pair_lr_d, s);
             const int64_t total = S.pair_off[npairs];
             double *T2 = D.setup_scratch<double>(ST_T2, total);
-            hipLaunchKernelGGL(k_t2, dim3(nblocks(total, 256)), dim3(256), 0, s, D.val, npairs, pc, pd, po, pe, pa,
-                               plc, pld, d_comp_rank, d_phig_off, d_phig, T2, total);
+            int64_t mmax = 1;   // most entries of a pair
+            for (int q = 0; q < npairs; ++q) mmax = std::max(mmax, S.pair_off[q + 1] - S.pair_off[q]);
+            hipLaunchKernelGGL(k_t2, dim3(npairs, unsigned((mmax + 63) / 64)), dim3(64), 0, s, D.val, pc, pd, po, pe,
+                               pa, plc, pld, d_comp_rank, d_phig_off, d_phig, T2);
             int64_t *st2 = D.setup_upload(S.a0seg2_tgt, s);
             int64_t *sp2 = D.setup_upload(S.a0seg2_ptr, s);
             int64_t *ss2 = D.setup_upload(S.a0seg2_src, s);
