@@ -73,6 +73,18 @@ struct Sell {
     const int16_t *dcol;   // column - row (null with col)
 };
 
+// Values of A from CSR into the slices (slot j of a row at off + SELL_C j + the
+// row's place; the padding stays as it is)
+__global__ __launch_bounds__(SELL_C) void k_sell_values(const int32_t *__restrict__ rowptr,
+                                                        const double *__restrict__ val,
+                                                        const int64_t *__restrict__ off, double *__restrict__ sv, int n) {
+    const int i = blockIdx.x * SELL_C + threadIdx.x;
+    if (i >= n) return;
+    double *o = sv + off[blockIdx.x] + threadIdx.x;
+    const int p0 = rowptr[i], p1 = rowptr[i + 1];
+    for (int p = p0; p < p1; ++p) o[int64_t(p - p0) * SELL_C] = val[p];
+}
+
 template <bool D16>
 __device__ __forceinline__ int sell_col(const Sell &A, int i, int64_t e) {
     if constexpr (D16)

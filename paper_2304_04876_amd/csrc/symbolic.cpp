@@ -1148,4 +1148,16 @@ gdsw_status analyze_batch(gdsw_handle_s *h, int32_t count, const gdsw_csr *A, co
     }
 }
 
+bool all_finite(const double *v, int64_t n) {
+    int bad = 0;
+#pragma omp parallel for reduction(| : bad) schedule(static) if (n > 200000)
+    for (int64_t p = 0; p < n; ++p) bad |= !std::isfinite(v[p]);
+    return bad == 0;
+}
+
+void copy_values(double *dst, const double *src, int64_t n) {
+#pragma omp parallel for schedule(static) num_threads(4) if (n > 200000)
+    for (int64_t p = 0; p < n; ++p) dst[p] = src[p];
+}
+
 }  // namespace gdsw
