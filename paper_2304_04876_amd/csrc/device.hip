@@ -647,15 +647,14 @@ static void factor_nd(gdsw_handle_s *h, int *d_status, hipStream_t s) {
     int32_t *d_up_n1 = D.setup_upload(N.up_n1, s);
     int64_t *d_up_rel = D.setup_upload(N.up_rel, s);
     int32_t *d_rel = D.setup_upload(N.rel, s);
-    hipLaunchKernelGGL(k_nd_factor<256>, dim3(S.np), dim3(256), 0, s, P64, D.nd_sn_ptr, D.nd_first, D.nd_ncol,
+    hipLaunchKernelGGL(k_nd_factor<1024>, dim3(S.np), dim3(1024), 0, s, P64, D.nd_sn_ptr, D.nd_first, D.nd_ncol,
                        D.nd_nrow, D.nd_voff, D.nd_st_ptr, d_up_ptr, d_up_k, d_up_s0, d_up_n1, d_up_rel, d_rel,
-                       d_status);
+                       D.ov_ptr, D.nd_row_sn, D.nd_lv_base, D.nd_lv_ptr, d_status);
     HIPCHK(hipGetLastError());
     check_status(D, d_status, S.np, s, "supernodal Cholesky");
     const size_t lds = sizeof(double) * size_t(std::max(N.max_ncol, 1));
     if (lds > D.max_lds) throw DevError{GDSW_ERR_INVALID_ARG, "a supernode is too wide for LDS"};
-    hipLaunchKernelGGL(k_nd_invert<256>, dim3(S.np), dim3(256), lds, s, P64, D.nd_sn_ptr, D.nd_ncol, D.nd_nrow,
-                       D.nd_voff);
+    hipLaunchKernelGGL(k_nd_invert<256>, dim3(unsigned(N.nsn)), dim3(256), lds, s, P64, D.nd_ncol, D.nd_nrow, D.nd_voff);
     HIPCHK(hipGetLastError());
     if (!D.ndL) D.ndL = D.raw_alloc(prec_size(prec) * size_t(std::max<int64_t>(nv, 1)));
     const dim3 gs(unsigned(N.nsn));

@@ -30,3 +30,20 @@ def _apply_matches(pr, tol=1e-12, Z=None, oracle_local="exact", coarse=None, **o
 @pytest.mark.parametrize("N,boxes", [(2, 1), (3, 1), (4, 1), (5, 1), (6, 1), (8, 1), (4, 2), (7, 3), (9, 2), (17, 2)])
 def test_band_cholesky(N, boxes):
     _apply_matches(P.poisson3d(N, boxes))
+
+
+# supernodes of one column up to separators of several blocks of 16 columns and
+# panels past the 64 rows one wavefront eliminates (17^3 and 20^3 in one part:
+# separators of more than 200 columns); leaves alone (3^3)
+@pytest.mark.parametrize("N,boxes", [(3, 1), (5, 1), (9, 1), (13, 1), (17, 1), (20, 1), (9, 2), (16, 2)])
+def test_supernodal_cholesky(N, boxes):
+    from paper_2304_04876_amd import binding as B
+    _apply_matches(P.poisson3d(N, boxes), exact_order=B.ORDER_ND)
+
+
+# right-hand sides of the extension on both sides of 16 (24 and more columns per
+# interior with rotations), interiors of less and more than one 64-row block
+@pytest.mark.parametrize("Ne,boxes,tol", [(6, 2, 1e-11), (8, 2, 1e-11), (9, 3, 1e-11)])
+def test_extension_many_columns(Ne, boxes, tol):
+    pr = P.elasticity_q1(Ne, boxes)
+    _apply_matches(pr, tol=tol, Z=P.rigid_body_modes(pr))   # (condition numbers up to 1e4)
