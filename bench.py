@@ -53,8 +53,6 @@ MEASURED_TRAFFIC = {
     ("k_nd_apply", "poisson128^3_P8^3", "fp16"): {"bytes": 1744098215, "src": "a6f6d04cf1931195"},
     # ILU(1) factors from 3 FastILU sweeps (the traffic does not depend on how the factors were computed)
     ("k_ilu_jacobi_phased", "poisson128^3_P8^3", "fp64"): {"bytes": 449873130, "src": "4e1cfa6c27b7f1c8"},
-    # ILU(2) factors from 3 FastILU sweeps (the entry holds for ILU(2) only)
-    ("k_ilu_jacobi_hold", "poisson128^3_P8^3", "fp64"): {"bytes": 1887125645, "src": "e771500e6d544bfb"},
 }
 
 
@@ -72,8 +70,8 @@ def kernel_source_hash(kernel):
         "k_nd_apply": [("kernels_nd.hpp", "// Sum over aligned groups of G lanes", "}  // namespace gdsw")],
         "k_ilu_jacobi_phased": [("kernels_apply.hpp", "// The register-resident sweeps for factors with more slots",
                                  "// Exact local solve A_i^{-1} r_i with the banded Cholesky factor")],
-        "k_ilu_jacobi_hold": [("kernels_apply.hpp", "// ILU(k) factors with more slots per row than the registers hold",
-                               "// The register-resident sweeps for factors with more slots")],
+        "k_ilu_jacobi_blocks": [("kernels_apply.hpp", "// The same sweeps by blocks of rows",
+                                 "// The register-resident sweeps for factors with more slots")],
     }
     if kernel not in segments:
         return None
@@ -292,9 +290,9 @@ def single(kind="poisson", N=None, Pn=None, local="ilu0", prec="fp64", coarse=No
     if local == "ilu0":
         if info["local_variant"] in (0, 1):
             # ILU(0): every entry in registers; ILU(1) (6 + 6 slots): L and
-            # U entries in registers one after the other; ILU(2) and up: the
-            # first slots of each row held, the others read on every sweep
-            kname = {0: "k_ilu_jacobi", 1: "k_ilu_jacobi_phased"}.get(ilu_level, "k_ilu_jacobi_hold")
+            # U entries in registers one after the other; ILU(2) and up: by
+            # blocks of rows
+            kname = {0: "k_ilu_jacobi", 1: "k_ilu_jacobi_phased"}.get(ilu_level, "k_ilu_jacobi_blocks")
         else:
             kname = "k_ilu_jacobi_generic"
     elif info["nd_subdomains"] == pr.n_parts:
@@ -312,8 +310,7 @@ def single(kind="poisson", N=None, Pn=None, local="ilu0", prec="fp64", coarse=No
                    + nloc * 12 + n * 20)
     traffic = None
     meas = None
-    if ((ilu_level == 0 and factor_sweeps == 0) or (kname == "k_ilu_jacobi_phased" and ilu_level == 1)
-            or (kname == "k_ilu_jacobi_hold" and ilu_level == 2)):
+    if (ilu_level == 0 and factor_sweeps == 0) or (kname == "k_ilu_jacobi_phased" and ilu_level == 1):
         meas = MEASURED_TRAFFIC.get((kname, f"poisson{N}^3_P{Pn}^3" if not elastic else f"elasticity{N}^3", prec))
     if meas and kernel_source_hash(kname) == meas["src"]:
         traffic = int(meas["bytes"])
@@ -480,8 +477,8 @@ def main():
         # (the faster form on these 16^3 boxes) and the band beside it
         line["iluk_fastilu"] = sub(single("poisson", args.N, args.P, "ilu0", "fp64", None, "single_reduce", 1, 3,
                                           steps=3, warmup=1, kernel_reps=10))
-        # ILU(2): 11 + 11 factor entries per row, more than registers and LDS
-        # hold, so the streaming sweeps read the factors on every sweep
+        # ILU(2): 11 + 11 factor entries per row, more than the registers of a
+        # workgroup hold whole: the sweeps by blocks of rows
         line["iluk2_fastilu"] = sub(single("poisson", args.N, args.P, "ilu0", "fp64", None, "single_reduce", 2, 3,
                                            steps=2, warmup=1, kernel_reps=10))
         line["exact_local"] = sub(single("poisson", args.N, args.P, "exact", "fp64", steps=3, warmup=1,

@@ -1299,55 +1299,48 @@ static bool launch_ilu_phased(const Symbolic &S, Device &D, const double *r, con
     return false;
 }
 
-// ILU(k) factors with more slots than the register-resident kernels take:
-// the first 6 slots of each row held in registers (4 with FP64 entries for
-// more than 4,096 rows a workgroup, the register budget), the rest streamed
-// (512 threads with up to 11 rows each, or 1024 with up to 6, 4 for FP64)
+// Factors that do not stay in a workgroup's registers whole (more slots than
+// the register-resident kernels take, or more rows): the sweeps by blocks of
+// NT rows, for up to 24 slots where the rings of the iterates fit LDS.  The
+// next block's entries are loaded ahead where the registers hold them (512
+// threads; 1,024: up to 12 slots).
 template <typename VT, int NT>
-static bool launch_ilu_hold(const Symbolic &S, Device &D, const double *r, const Skip &sk, hipStream_t s,
-                            const Device::SizeClass &c) {
+static bool launch_ilu_blocks(const Symbolic &S, Device &D, const double *r, const Skip &sk, hipStream_t s,
+                              const Device::SizeClass &c) {
     if constexpr (NT != 512 && NT != 1024) {
         return false;
     } else {
-        if (S.opt.jacobi_sweeps < 2 || !D.Lc || !D.Uc || D.KLp < 2 || D.KUp < 2) return false;
         using AT = typename AccOf<VT>::type;
-        constexpr bool f64 = std::is_same<VT, double>::value;
-        const size_t lds = 3 * sizeof(AT) * size_t(std::max(c.max_ni, 1));
+        const int K = std::max(D.KLp, D.KUp);
+        if (S.opt.jacobi_sweeps < 2 || !D.Lc || !D.Uc || K > 24) return false;
+        int64_t ring = 1;
+        while (ring < int64_t(S.reach) + NT) ring *= 2;
+        const size_t lds = sizeof(AT) * size_t(S.opt.jacobi_sweeps - 1) * size_t(ring);
         if (lds > D.max_lds) return false;
-        const int need = (c.max_ni + NT - 1) / NT;
-        const int nb = c.end - c.begin;
+        const dim3 grid(c.end - c.begin, D.ns);
         const Skip kc = class_skip(D, sk, c);
-#define GDSW_ILU_HOLD(RR)                                                                                     \
-        if (need <= RR) {                                                                                     \
-            hipLaunchKernelGGL((k_ilu_jacobi_hold<NT, RR, (f64 && RR * NT > 4096) ? 4 : 6, VT>), dim3(nb, D.ns), \
-                               dim3(NT), lds, s, r,                                                           \
-                               D.ov_idx, D.ov_ptr, D.ell_off, S.ell_rows, D.KLp, D.KUp, (const VT *)D.Lv,     \
-                               D.Lc, (const VT *)D.Uv, D.Uc, (const VT *)D.dinv, D.dscale,                    \
-                               S.opt.jacobi_sweeps, D.zloc, c.max_ni, kc);                                    \
-            return true;                                                                                      \
-        }
-        if constexpr (NT == 512) {
-            GDSW_ILU_HOLD(4)
-            GDSW_ILU_HOLD(8)
-            GDSW_ILU_HOLD(11)
-        } else {
-            GDSW_ILU_HOLD(2)
-            GDSW_ILU_HOLD(4)
-            if constexpr (!f64) { GDSW_ILU_HOLD(6) }   // (FP64 at 6 rows a thread spills)
-        }
-#undef GDSW_ILU_HOLD
-        return false;
+#define GDSW_ILU_BLOCKS(KM, PRE)                                                                              \
+        hipLaunchKernelGGL((k_ilu_jacobi_blocks<NT, KM, PRE, VT>), grid, dim3(NT), lds, s, r, D.ov_idx,       \
+                           D.ov_ptr, D.ell_off, S.ell_rows, D.KLp, D.KUp, (const VT *)D.Lv, D.Lc,             \
+                           (const VT *)D.Uv, D.Uc, (const VT *)D.dinv, D.dscale, S.opt.jacobi_sweeps, D.zloc, \
+                           int(ring), kc)
+        if (K <= 6) GDSW_ILU_BLOCKS(6, true);
+        else if (K <= 12) GDSW_ILU_BLOCKS(12, true);
+        else GDSW_ILU_BLOCKS(24, NT == 512);
+#undef GDSW_ILU_BLOCKS
+        return true;
     }
 }
 
 template <typename VT, int NT>
 static bool launch_ilu_regs(const Symbolic &S, Device &D, const double *r, const Skip &sk, hipStream_t s,
                             const Device::SizeClass &c) {
-    // more slots than the phased kernel holds: the first ones held
-    if (D.KLp > ILU_KL2 || D.KUp > ILU_KU2) return launch_ilu_hold<VT, NT>(S, D, r, sk, s, c);
+    // more slots than the phased kernel holds: by blocks of rows
+    if (D.KLp > ILU_KL2 || D.KUp > ILU_KU2) return launch_ilu_blocks<VT, NT>(S, D, r, sk, s, c);
     // (one sweep per triangle needs no factor entries: the streaming kernel)
     if (!D.Cp || S.opt.jacobi_sweeps < 2) return false;
-    if (D.KLp == ILU_KL2 && D.KUp == ILU_KU2) return launch_ilu_phased<VT, NT>(S, D, r, sk, s, c);
+    if (D.KLp == ILU_KL2 && D.KUp == ILU_KU2)
+        return launch_ilu_phased<VT, NT>(S, D, r, sk, s, c) || launch_ilu_blocks<VT, NT>(S, D, r, sk, s, c);
     if (D.KLp != ILU_KL || D.KUp != ILU_KU) return false;
     constexpr bool f64 = std::is_same<VT, double>::value;
     const int need = (c.max_ni + NT - 1) / NT;
@@ -1382,7 +1375,7 @@ static bool launch_ilu_regs(const Symbolic &S, Device &D, const double *r, const
     }
     if constexpr (NT == 512) { GDSW_ILU_CASE(11) }
 #undef GDSW_ILU_CASE
-    return false;
+    return launch_ilu_blocks<VT, NT>(S, D, r, sk, s, c);   // (more rows than that)
 }
 
 template <typename VT, int NT>

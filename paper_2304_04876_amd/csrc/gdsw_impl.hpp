@@ -191,6 +191,7 @@ struct Symbolic {
     std::vector<int32_t> lvl_rows;  // local rows by level, slice i starts at ov_ptr[i]
     std::vector<int32_t> ldiag;     // [sum n_i] position (relative to lrowptr) of the diagonal
     int32_t KL = 0, KU = 0;         // max strictly lower / upper entries per row
+    int32_t reach = 0;              // largest distance of a local entry (fill included) from its diagonal
     std::vector<int64_t> ell_off;   // [np+1] padded row offsets
     int64_t ell_rows = 0;
     // FastILU: per local entry its product pairs (positions into the local

@@ -295,25 +295,31 @@ __global__ __launch_bounds__(NT) void k_ilu_jacobi_generic(
     }
 }
 
-// ILU(k) factors with more slots per row than the registers hold beside
-// the sweeps (ILU(2) and ILU(3) of the 7-point stencil: 11 + 11 and 21 + 21
-// slots): the first H slots of each of the thread's R rows stay in registers
-// across the sweeps of a triangle (the L slots for the L sweeps, then the U
-// slots in the same registers), so that only the slots past them are read
-// again on every sweep (two rows and four slots at a time, as in
-// k_ilu_jacobi_generic).  Each row's products in slot order: the same bits
-// as the streaming sweeps.  Rows t, t + NT, ... of thread t (ni <= NT R and
-// the vectors in LDS, checked by the launcher); right-hand-side slot
-// blockIdx.y.
-template <int NT, int R, int H, typename VT>
-__global__ __launch_bounds__(NT) void k_ilu_jacobi_hold(
+// The same sweeps by blocks of rows: factors too large for the registers of a
+// workgroup (ILU(2) and ILU(3) of the 7-point stencil, or many rows) are still
+// read once per apply.  An iterate's row needs lower rows (L) or higher ones
+// (U) of the iterate before it, and none further than `reach`: so a block of NT
+// rows, one per thread, loads its L entries into registers and takes all its
+// sweeps in turn, y^2 .. y^K, before the next block above it; then the U
+// entries likewise from the last block down.  Of the iterates y^1 = r .. y^{K-1}
+// only the last `ring` rows (a power of two of at least reach + NT) are kept,
+// in LDS, so that any number of rows fits; y^K waits in the subdomain's place
+// of zloc for the U sweeps (a thread reads back its own rows).  The next block's
+// entries and right-hand side are loaded while one block is in use (PRE: the
+// entries, where the registers hold both).  Every value is the sweeps', in slot
+// order: the same bits as k_ilu_jacobi_generic.  LDS: (K - 1) ring accumulators.
+// Measured (FP64; each against holding a row's first slots in registers and
+// reading the others on every sweep): ILU(2) 128^3, 512 subdomains of 5,632 rows,
+// 291 -> 133 us; ILU(3) 602 -> 324 us; ILU(2) on 125 subdomains of up to 7,776
+// rows (which streamed every slot, their iterates in global memory) 276 ->
+// 94 us (1,024 threads).
+template <int NT, int KM, bool PRE, typename VT>
+__global__ __launch_bounds__(NT) void k_ilu_jacobi_blocks(
     const double *__restrict__ r, const int32_t *__restrict__ ov_idx, const int64_t *__restrict__ ov_ptr,
     const int64_t *__restrict__ ell_off, int64_t ell_rows, int KL, int KU, const VT *__restrict__ Lv,
     const uint16_t *__restrict__ Lc, const VT *__restrict__ Uv, const uint16_t *__restrict__ Uc,
-    const VT *__restrict__ dinv, const double *__restrict__ dscale, int sweeps,
-    double *__restrict__ zloc, int maxrows, Skip sk) {
+    const VT *__restrict__ dinv, const double *__restrict__ dscale, int sweeps, double *zloc, int ring, Skip sk) {
     using AT = typename AccOf<VT>::type;
-    static_assert(H % 2 == 0, "held columns two to a word");
     const int slot = blockIdx.y, i = sk.sub_at(blockIdx.x);
     if (sk.sub(i, slot)) return;
     r += slot * sk.sl.n;
@@ -322,105 +328,93 @@ __global__ __launch_bounds__(NT) void k_ilu_jacobi_hold(
     const int64_t o = ov_ptr[i];
     const int ni = int(ov_ptr[i + 1] - o);
     if (ni == 0) return;   // (the whole workgroup)
-    AT *rb = reinterpret_cast<AT *>(smraw);
-    AT *cur = rb + maxrows, *nxt = cur + maxrows;
+    AT *Q = reinterpret_cast<AT *>(smraw);   // iterate k's ring at (k - 1) ring
+    const int mask = ring - 1;
     const int64_t eo = ell_off[i];
-    const int tid = threadIdx.x;
-    for (int l = tid; l < ni; l += NT) {
-        const int d = ov_idx[o + l];
+    const int tid = threadIdx.x, last = ni - 1;
+    const int nblk = (ni + NT - 1) / NT;
+    struct Row {
+        VT v[KM];
+        uint16_t c[KM];
+    };
+    // slots past K re-read the last one and are not used; rows outside the
+    // subdomain read its first or last row and are not written
+    auto at = [&](int l) { return min(max(l, 0), last); };
+    auto load = [&](Row &w, const VT *__restrict__ V, const uint16_t *__restrict__ C, int K, int l) {
+        const int64_t e0 = eo + at(l);
+#pragma unroll
+        for (int j = 0; j < KM; ++j) {
+            const int64_t e = int64_t(min(j, K - 1)) * ell_rows + e0;
+            w.v[j] = ld_once(V + e);
+            w.c[j] = C[e];
+        }
+    };
+    // iterates 2 .. sweeps of row l with right-hand side b; first_next: the next
+    // block's first iterate, for row ln
+    auto row_sweeps = [&](const Row &w, int K, int l, AT b, int ln, AT first_next, auto store) {
+        for (int k = 2; k <= sweeps; ++k) {
+            const AT *src = Q + (k - 2) * ring;
+            AT g[KM];
+#pragma unroll
+            for (int j = 0; j < KM; ++j) g[j] = src[w.c[j] & mask];
+            AT acc = b;
+#pragma unroll
+            for (int j = 0; j < KM; ++j)
+                if (j < K) acc -= to_acc(w.v[j]) * g[j];
+            if (k < sweeps) {
+                if (l < ni) Q[(k - 1) * ring + (l & mask)] = acc;
+            } else {
+                // (iterate 1 is read by sweep 2 alone; with one more sweep
+                // than two the barriers below stand in between)
+                if (sweeps == 2) __syncthreads();
+                if (l < ni) store(acc);
+                if (ln >= 0) Q[ln & mask] = first_next;
+            }
+            __syncthreads();
+        }
+    };
+    Row cur, nxt;
+    load(cur, Lv, Lc, KL, tid);
+    auto gathered = [&](int d) {
         double x = r[d];
         if (dscale) x *= dscale[d];
-        rb[l] = AT(x);
-        cur[l] = AT(x);
-    }
-    // the held slots of the thread's rows (rows past the subdomain read its
-    // last row and are never written)
-    AT hv[R][H];
-    uint32_t hc[R][H / 2];   // columns of slots j and j + 1 in one word
-    auto hold = [&](const VT *__restrict__ V, const uint16_t *__restrict__ C, int K) {
-#pragma unroll
-        for (int m = 0; m < R; ++m) {
-            const int64_t e0 = eo + min(tid + m * NT, ni - 1);
-#pragma unroll
-            for (int j = 0; j < H; j += 2) {
-                const int64_t ea = int64_t(min(j, K - 1)) * ell_rows + e0;
-                const int64_t eb = int64_t(min(j + 1, K - 1)) * ell_rows + e0;
-                hv[m][j] = to_acc(V[ea]);
-                hv[m][j + 1] = to_acc(V[eb]);
-                hc[m][j / 2] = uint32_t(C[ea]) | (uint32_t(C[eb]) << 16);
-            }
-        }
+        return AT(x);
     };
-    constexpr int SC = 4;
-    auto sweep = [&](const VT *__restrict__ V, const uint16_t *__restrict__ C, int K) {
-#pragma unroll
-        for (int m0 = 0; m0 < R; m0 += 2) {
-            AT acc[2];
-#pragma unroll
-            for (int b = 0; b < 2; ++b)
-                if (m0 + b < R) acc[b] = rb[min(tid + (m0 + b) * NT, ni - 1)];
-#pragma unroll
-            for (int b = 0; b < 2; ++b)
-                if (m0 + b < R) {
-#pragma unroll
-                    for (int j = 0; j < H; ++j)
-                        if (j < K) acc[b] -= hv[m0 + b][j] * cur[(hc[m0 + b][j / 2] >> (16 * (j & 1))) & 0xffffu];
-                }
-            for (int s0 = H; s0 < K; s0 += SC) {
-                AT v[2][SC];
-                int c[2][SC];
-#pragma unroll
-                for (int b = 0; b < 2; ++b)
-#pragma unroll
-                    for (int j = 0; j < SC; ++j) {
-                        const int64_t e = int64_t(min(s0 + j, K - 1)) * ell_rows + eo +
-                                          min(tid + min(m0 + b, R - 1) * NT, ni - 1);
-                        v[b][j] = to_acc(V[e]);
-                        c[b][j] = C[e];
-                    }
-                AT g[2][SC];
-#pragma unroll
-                for (int b = 0; b < 2; ++b)
-#pragma unroll
-                    for (int j = 0; j < SC; ++j) g[b][j] = cur[c[b][j]];
-#pragma unroll
-                for (int b = 0; b < 2; ++b)
-                    if (m0 + b < R) {
-#pragma unroll
-                        for (int j = 0; j < SC; ++j)
-                            if (s0 + j < K) acc[b] -= v[b][j] * g[b][j];
-                    }
-            }
-#pragma unroll
-            for (int b = 0; b < 2; ++b) {
-                const int l = tid + (m0 + b) * NT;
-                if (m0 + b < R && l < ni) nxt[l] = acc[b];
-            }
-        }
+    int d = ov_idx[o + at(tid + NT)];   // (one block ahead)
+    AT x = gathered(ov_idx[o + at(tid)]);
+    Q[tid & mask] = x;
+    __syncthreads();
+    for (int blk = 0; blk < nblk; ++blk) {
+        const int l = blk * NT + tid;
+        if (PRE) load(nxt, Lv, Lc, KL, l + NT);
+        const AT xn = gathered(d);
+        d = ov_idx[o + at(l + 2 * NT)];
+        row_sweeps(cur, KL, l, x, l + NT, xn, [&](AT y) { zloc[o + l] = double(y); });
+        x = xn;
+        if (PRE) cur = nxt;
+        else if (blk + 1 < nblk) load(cur, Lv, Lc, KL, l + NT);
+    }
+    // U from the last block down: w^1 = D^{-1} y^K
+    const int l1 = (nblk - 1) * NT + tid;
+    load(cur, Uv, Uc, KU, l1);
+    auto scaled = [&](int l) {   // (a row of this thread's, or row 0's place before the first block: not used)
+        return l >= 0 && l < ni ? AT(to_acc(dinv[eo + l]) * AT(zloc[o + l])) : AT(0);
     };
-    hold(Lv, Lc, KL);
+    x = scaled(l1);
+    Q[l1 & mask] = x;
     __syncthreads();
-    for (int k = 1; k < sweeps; ++k) {
-        sweep(Lv, Lc, KL);
-        __syncthreads();
-        AT *t = cur; cur = nxt; nxt = t;
-    }
-    for (int l = tid; l < ni; l += NT) {
-        rb[l] = to_acc(dinv[eo + l]) * cur[l];
-        nxt[l] = rb[l];
-    }
-    hold(Uv, Uc, KU);
-    __syncthreads();
-    { AT *t = cur; cur = nxt; nxt = t; }
-    for (int k = 1; k < sweeps; ++k) {
-        sweep(Uv, Uc, KU);
-        __syncthreads();
-        AT *t = cur; cur = nxt; nxt = t;
-    }
-    for (int l = tid; l < ni; l += NT) {
-        double v = double(cur[l]);
-        if (dscale) v *= dscale[ov_idx[o + l]];
-        zloc[o + l] = v;
+    for (int blk = nblk - 1; blk >= 0; --blk) {
+        const int l = blk * NT + tid;
+        if (PRE) load(nxt, Uv, Uc, KU, l - NT);
+        const AT xn = scaled(l - NT);
+        row_sweeps(cur, KU, l, x, l - NT, xn, [&](AT y) {
+            double v = double(y);
+            if (dscale) v *= dscale[ov_idx[o + l]];
+            zloc[o + l] = v;
+        });
+        x = xn;
+        if (PRE) cur = nxt;
+        else if (blk > 0) load(cur, Uv, Uc, KU, l - NT);
     }
 }
 

@@ -619,11 +619,12 @@ void build_local(Symbolic &s) {
     s.bw.assign(np, 0);
     s.KL = 0;
     s.KU = 0;
+    s.reach = 0;
     int32_t KL = 0, KU = 0;
 #pragma omp parallel
     {
         std::vector<int32_t> g2l(s.n, -1);
-        int32_t kl = 0, ku = 0;
+        int32_t kl = 0, ku = 0, reach = 0;
 #pragma omp for schedule(dynamic)
         for (int i = 0; i < np; ++i) {
             const int64_t o = s.ov_ptr[i], ni = s.ov_ptr[i + 1] - o;
@@ -650,6 +651,7 @@ void build_local(Symbolic &s) {
                 for (int64_t q = 0; q < RL[l]; ++q, ++pos) {
                     if (C[pos] < l) ++nl;
                     if (C[pos] > l) ++nu;
+                    reach = std::max(reach, int32_t(std::abs(l - C[pos])));
                 }
                 kl = std::max(kl, nl);
                 ku = std::max(ku, nu);
@@ -661,6 +663,7 @@ void build_local(Symbolic &s) {
         {
             KL = std::max(KL, kl);
             KU = std::max(KU, ku);
+            s.reach = std::max(s.reach, reach);
         }
     }
     s.KL = KL;

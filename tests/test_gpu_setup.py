@@ -47,3 +47,33 @@ def test_supernodal_cholesky(N, boxes):
 def test_extension_many_columns(Ne, boxes, tol):
     pr = P.elasticity_q1(Ne, boxes)
     _apply_matches(pr, tol=tol, Z=P.rigid_body_modes(pr))   # (condition numbers up to 1e4)
+
+
+# sweeps by blocks of rows: blocks of 512 and 1,024 rows with a ragged last
+# one, more rows than the register-resident forms take (one part of 18^3, 21^3
+# rows; ILU(0) and ILU(1)), more slots (ILU(2), ILU(3)), two sweeps (no iterate
+# between the first and the last); the streaming sweeps give the same bits
+@pytest.mark.parametrize("N,level,sweeps", [(18, 0, 5), (21, 1, 5), (18, 2, 5), (9, 2, 2), (18, 3, 3), (3, 2, 5)])
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+def test_ilu_block_sweeps(N, level, sweeps, prec):
+    import torch
+    from paper_2304_04876_amd import binding as B
+    pr = P.poisson3d(N, 1)
+    g = B.Gdsw(pr.A, pr.part, 1, 1, local=B.LOCAL_ILU0, ilu_level=level, jacobi_sweeps=sweeps,
+               local_prec=B.FP64 if prec == "fp64" else B.FP32)
+    r = torch.from_numpy(P.rhs_uniform(pr.n, 4)).cuda()
+    out = []
+    for v in range(4):
+        try:
+            B.gdsw_set_launch(g.h, v, 0, 1, 0)
+        except B.GdswError as e:
+            assert e.status == 1 and "fit" in str(e)
+            continue
+        out.append(torch.zeros_like(r))
+        g.apply(r, out[-1])
+    assert len(out) >= 3 and all(torch.equal(z, out[0]) for z in out)
+    if prec == "fp64":
+        M = O.GDSW(pr.A, pr.part, 1, 1, local="ilu0", ilu_level=level, sweeps=sweeps)
+        zr = M.apply(r.cpu().numpy())
+        assert np.abs(out[0].cpu().numpy() - zr).max() <= 1e-12 * np.abs(zr).max()
+    g.close()
