@@ -1502,16 +1502,23 @@ static bool launch_local_variant(const Symbolic &S, Device &D, int v, const doub
 // Every size class in the configuration tuned for it, else the handle's
 // (gdsw_set_launch / gdsw_autotune), else the fixed rule: register-resident
 // sweeps when they fit (FP64: 512 threads, reduced precision: 1024), else
-// streaming; band solves with 512 threads.
+// streaming; exact solves with 1024 threads where every subdomain gets a
+// compute unit of its own, else 512.
 template <typename VT>
 static void launch_local_class(const Symbolic &S, Device &D, const double *r, const Skip &sk, hipStream_t s,
                                const Device::SizeClass &c) {
     if (c.variant >= 0 && launch_local_variant<VT>(S, D, c.variant, r, sk, s, c)) return;
     if (D.local_variant >= 0 && launch_local_variant<VT>(S, D, D.local_variant, r, sk, s, c)) return;
     static const int ilu_order_f64[N_ILU_VARIANTS] = {0, 1, 2, 3}, ilu_order_lo[N_ILU_VARIANTS] = {1, 0, 2, 3},
-                     band_order[N_BAND_VARIANTS] = {1, 0, 2, 4, 3, 5};
+                     band_order[N_BAND_VARIANTS] = {1, 0, 2, 4, 3, 5}, band_order_few[N_BAND_VARIANTS] = {2, 1, 0, 4, 3, 5};
     const bool ilu = S.opt.local == GDSW_LOCAL_ILU0;
-    const int *order = ilu ? (std::is_same<VT, double>::value ? ilu_order_f64 : ilu_order_lo) : band_order;
+    // at most one exact solve per compute unit: 1,024 threads each (band: 8
+    // subdomains of 1,331 rows FP64 224 -> 168 us per launch against 512, 216 of
+    // 2,700 FP32 521 -> 375; supernodal: 216 of 5,632 FP64 871 -> 689; with 512
+    // subdomains, two per unit, 512 threads win: 1.33 against 1.43 ms)
+    const bool few = int64_t(c.end - c.begin) * D.ns <= D.n_cu;
+    const int *order = ilu ? (std::is_same<VT, double>::value ? ilu_order_f64 : ilu_order_lo)
+                           : few ? band_order_few : band_order;
     const int nv = ilu ? N_ILU_VARIANTS : N_BAND_VARIANTS;
     for (int q = 0; q < nv; ++q)
         if (launch_local_variant<VT>(S, D, order[q], r, sk, s, c)) return;
