@@ -866,7 +866,10 @@ __device__ void band_llt_solve_ahead(const VT *__restrict__ L, int n, int b, AT 
     static_assert(LPR == 16, "the row sums use rows of 16 lanes");
     constexpr int PF = F64 ? 4 : 6;      // forward: row groups of RPI rows held per step
     constexpr int RB = F64 ? 2 : 4;      // forward: row groups per pass past the held ones
-    constexpr int BPF = F64 ? 16 : 32;   // backward: rows of the thread's first column held
+    // backward: rows of the thread's first column held (FP32 all 64 of a block:
+    // 375 -> 365 us on 216 subdomains of 2,700 rows against 32, 400 -> 389 on
+    // 48^3 elasticity; FP64 with 32 spills, 168 -> 223)
+    constexpr int BPF = F64 ? 16 : 64;
     constexpr int G = F64 ? 8 : 32;      // backward: loads per group past the held rows
     const int64_t w = b + 1;
     const int tid = threadIdx.x, lane = tid & 63;
