@@ -345,7 +345,12 @@ __device__ __forceinline__ int lanes_for(int items, int work, int gmin) {
 // leaves need neither the pass-result buffer nor a workgroup barrier
 // between (4) and (5).  The subdomain's supernode table and each row's
 // supernode are copied to LDS first, so that an item's factor loads wait on
-// one global load at most.  w: one vector of struct-entry length per slot
+// one global load at most.  Bound by those loads' latency and by the
+// instructions around them: eight terms a lane in flight (4: 1.27 / 1.36 /
+// 0.66 ms, 8: 1.27 / 1.29 / 0.65, 16: 1.43 / 1.47 / 0.75 per launch on 128^3
+// FP64, 16 packed diffusion problems FP32, 96^3 FP64), the forward gathers
+// by four and a struct entry's supernode read a round ahead (together 1.33 /
+// 1.41 / 0.69 before, with four terms).  w: one vector of struct-entry length per slot
 // (slot stride nst).  LDS: nd_lds_bytes(maxrows, maxt, maxsn, accumulator
 // size) (gdsw_impl.hpp).
 template <int NT, typename VT>
@@ -408,7 +413,7 @@ __global__ __launch_bounds__(NT) void k_nd_apply(
                     const int4 J = snt[rsn[rr]];
                     const int c0 = rr - J.x;
                     const VT *row = Li + J.w + c0;
-#pragma unroll 4
+#pragma unroll 8
                     for (int c = 0; c <= c0; ++c) acc += to_acc(row[int64_t(c) * J.y]) * y[J.x + c];
                 }
                 __builtin_amdgcn_wave_barrier();
@@ -419,7 +424,19 @@ __global__ __launch_bounds__(NT) void k_nd_apply(
             for (int rr = R0 + tid; rr < R1; rr += NT) {
                 AT acc = y[rr];
                 const int64_t e1 = rc_ptr[o + rr + 1];
-                for (int64_t e = rc_ptr[o + rr]; e < e1; ++e) acc -= wi[rc_w[e]];
+                // (four products' places, then the products, read together;
+                // past the last one it is read again and not used)
+                for (int64_t e = rc_ptr[o + rr]; e < e1; e += 4) {
+                    int at[4];
+                    AT v[4];
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) at[u] = rc_w[min(e + u, e1 - 1)];
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) v[u] = wi[at[u]];
+#pragma unroll
+                    for (int u = 0; u < 4; ++u)
+                        if (e + u < e1) acc -= v[u];
+                }
                 t[rr - R0] = acc;
             }
             __syncthreads();
@@ -431,7 +448,7 @@ __global__ __launch_bounds__(NT) void k_nd_apply(
                 const VT *row = Li + J.w + c0;
                 const AT *tJ = t + (J.x - R0);
                 AT acc = 0;
-#pragma unroll 4
+#pragma unroll 8
                 for (int c = g; c <= c0; c += G) acc += to_acc(row[int64_t(c) * J.y]) * tJ[c];
                 acc = group_sum(acc, G);
                 if (g == 0) y[rr] = acc;
@@ -441,13 +458,15 @@ __global__ __launch_bounds__(NT) void k_nd_apply(
         // (3)
         {
             const int G = lanes_for(T1 - T0, a.z, 1), g = tid & (G - 1);
+            int kn = T0 < T1 ? st_sn[sb + min(T0 + tid / G, T1 - 1)] : 0;   // (one round ahead)
             for (int q = T0 + tid / G; q < T1; q += NT / G) {
-                const int k0 = int(st_sn[sb + q] - s0);
+                const int k0 = int(kn - s0);
+                kn = st_sn[sb + min(q + NT / G, T1 - 1)];
                 const int4 K = snt[k0];
                 const int ns = K.z - K.y;
                 const VT *row = Li + K.w + int64_t(K.y) * K.y + (q - stp[k0]);
                 AT acc = 0;
-#pragma unroll 4
+#pragma unroll 8
                 for (int k = g; k < K.y; k += G) acc += to_acc(row[int64_t(k) * ns]) * y[K.x + k];
                 acc = group_sum(acc, G);
                 if (g == 0) wi[q] = acc;
@@ -468,7 +487,7 @@ __global__ __launch_bounds__(NT) void k_nd_apply(
                 const VT *col = Li + J.w + int64_t(J.y) * J.y + int64_t(rr - J.x) * ns;
                 const int32_t *srow = st_row + sb + stp[j0];
                 AT acc = 0;
-#pragma unroll 4
+#pragma unroll 8
                 for (int q = g; q < ns; q += G) acc += to_acc(col[q]) * y[srow[q]];
                 acc = group_sum(acc, G);
                 if (g == 0) t[rr - R0] = y[rr] - acc;
@@ -484,7 +503,7 @@ __global__ __launch_bounds__(NT) void k_nd_apply(
                 const VT *col = Li + J.w + int64_t(c) * J.y;
                 const AT *tJ = t + (J.x - R0);
                 AT acc = 0;
-#pragma unroll 4
+#pragma unroll 8
                 for (int k = c + g; k < J.y; k += G) acc += to_acc(col[k]) * tJ[k];
                 acc = group_sum(acc, G);
                 if (g == 0) y[rr] = acc;
@@ -504,7 +523,7 @@ __global__ __launch_bounds__(NT) void k_nd_apply(
             const int ns = J.z - J.y;
             const VT *col = Li + J.w + int64_t(J.y) * J.y + int64_t(rr - J.x) * ns;
             const int32_t *srow = st_row + sb + stp[j0];
-#pragma unroll 4
+#pragma unroll 8
             for (int q = 0; q < ns; ++q) acc += to_acc(col[q]) * y[srow[q]];
             acc = y[rr] - acc;
         }
@@ -515,7 +534,7 @@ __global__ __launch_bounds__(NT) void k_nd_apply(
         if (in) {
             const int c = rr - J.x;
             const VT *col = Li + J.w + int64_t(c) * J.y;
-#pragma unroll 4
+#pragma unroll 8
             for (int k = c; k < J.y; ++k) acc += to_acc(col[k]) * y[J.x + k];
         }
         __builtin_amdgcn_wave_barrier();
