@@ -850,6 +850,32 @@ __device__ __forceinline__ void band_store_triangle(const AT (&tv)[tri_per_threa
     }
 }
 
+// Band entries from `base` on by buffer loads: an offset (bytes) past the
+// last entry reads as zero, which is how entries outside the band are left
+// out (offset BAND_NONE) without a branch around each load, and an offset
+// fixed over the steps needs no arithmetic in them.  base: uniform over the
+// workgroup; left: the entries from it to the end of the subdomain's band.
+// Offsets used with it stay under 2^31 - 4,096: 448 rows of a band at most.
+constexpr int BAND_NONE = int(0x80000000u);
+
+template <typename VT>
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t band_window(const VT *base, int64_t left) {
+    const uint64_t a = reinterpret_cast<uint64_t>(base);
+    const uint32_t lo = __builtin_amdgcn_readfirstlane(uint32_t(a)), hi = __builtin_amdgcn_readfirstlane(uint32_t(a >> 32));
+    const int bytes = __builtin_amdgcn_readfirstlane(int(min(max(left, int64_t(0)) * int64_t(sizeof(VT)), int64_t(0x7fffffff))));
+    return __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void *>(uint64_t(hi) << 32 | lo), 0, bytes, 0x00020000);
+}
+
+template <typename VT>
+__device__ __forceinline__ auto band_window_ld(__amdgpu_buffer_rsrc_t win, int at) {
+    if constexpr (sizeof(VT) == 8)   // (non-temporal, as band_ld)
+        return to_acc(__builtin_bit_cast(VT, __builtin_amdgcn_raw_buffer_load_b64(win, at, 0, 2)));
+    else if constexpr (sizeof(VT) == 4)
+        return to_acc(__builtin_bit_cast(VT, __builtin_amdgcn_raw_buffer_load_b32(win, at, 0, 0)));
+    else
+        return to_acc(__builtin_bit_cast(VT, __builtin_amdgcn_raw_buffer_load_b16(win, at, 0, 0)));
+}
+
 // The solve with its band loads one block step ahead (1024 threads).  A
 // step first uses the entries loaded during the step before (the rows below
 // the solved block, forward; the thread's column above it, backward),
@@ -858,7 +884,13 @@ __device__ __forceinline__ void band_store_triangle(const AT (&tv)[tri_per_threa
 // barriers instead of being waited for at the start of the next step.  Rows
 // (columns) past the held ones are loaded in the step itself.  Every sum is
 // formed in the same order as in the plain form below, so both give the
-// same bits.
+// same bits.  Bound by the instructions of a step's critical path: with a
+// test and a 64-bit address per load and a branch around it, the loads of a
+// step took longer to issue than to arrive; through the window (band_window)
+// the forward step issues its 28 with a handful of scalar instructions: 365
+// -> 268 us per launch on 216 subdomains of 2,700 rows FP32, 331 -> 226 on 27
+// of elasticity, 389 -> 319 on 48^3 elasticity, 154 -> 139 on 8 of 1,331 rows
+// FP64.
 template <typename VT, typename AT, int NT, bool INV>
 __device__ void band_llt_solve_ahead(const VT *__restrict__ L, int n, int b, AT *y, AT *sT) {
     constexpr bool F64 = sizeof(AT) == 8;
@@ -868,8 +900,9 @@ __device__ void band_llt_solve_ahead(const VT *__restrict__ L, int n, int b, AT 
     constexpr int RB = F64 ? 2 : 4;      // forward: row groups per pass past the held ones
     // backward: rows of the thread's first column held (FP32 all 64 of a block:
     // 375 -> 365 us on 216 subdomains of 2,700 rows against 32, 400 -> 389 on
-    // 48^3 elasticity; FP64 with 32 spills, 168 -> 223)
-    constexpr int BPF = F64 ? 16 : 64;
+    // 48^3 elasticity; FP64 32, the registers' limit: 154 -> 139 on 8 of 1,331
+    // rows against 16)
+    constexpr int BPF = F64 ? 32 : 64;
     constexpr int G = F64 ? 8 : 32;      // backward: loads per group past the held rows
     const int64_t w = b + 1;
     const int tid = threadIdx.x, lane = tid & 63;
@@ -880,18 +913,30 @@ __device__ void band_llt_solve_ahead(const VT *__restrict__ L, int n, int b, AT 
     // v[it][q] = L(r, k0 + sub + 16 q) for the row r = k0 + 64 + it RPI + rg
     // below the block at k0 (zero outside the band and past the subdomain)
     AT v[PF][QN];
-    auto load_rows = [&](int k0) {
-        const int k1 = k0 + BS_NB, rend = min(n, k1 + b);
+    constexpr int VS = sizeof(VT);
+    const int64_t len = int64_t(n) * w;
+    // entry (k0 + i, k0 + c) lies i b + c entries after entry (k0, k0), so a
+    // lane's offsets are the same in every step; rows past the subdomain are
+    // past the window
+    auto load_rows = [&](int k0) __attribute__((always_inline)) {
+        const int64_t at0 = int64_t(k0) * w + b;
+        const __amdgpu_buffer_rsrc_t win = band_window(L + at0, len - at0);
 #pragma unroll
         for (int it = 0; it < PF; ++it) {
-            const int r = k1 + it * RPI + rg;
-            const int s0 = max(0, r - b - k0);
-            const VT *row = L + int64_t(r) * w + (k0 - r + b);
+            const int i = BS_NB + it * RPI + rg;
+            const int at = (i * b + sub) * VS;
 #pragma unroll
-            for (int q = 0; q < QN; ++q) {
-                const int s = sub + q * LPR;
-                v[it][q] = (r < rend && s >= s0) ? to_acc(band_ld(&row[s])) : AT(0);
-            }
+            for (int q = 0; q < QN; ++q)
+                v[it][q] = band_window_ld<VT>(win, sub + q * LPR >= i - b ? at + q * LPR * VS : BAND_NONE);
+        }
+    };
+    auto load_triangle = [&](int k0) __attribute__((always_inline)) {
+        const int64_t at0 = int64_t(k0) * w + b;
+        const __amdgpu_buffer_rsrc_t win = band_window(L + at0, len - at0);
+#pragma unroll
+        for (int c = 0; c < tri_per_thread<NT>(); ++c) {
+            const int e = tid + c * NT, t = e / BS_NB, q = e % BS_NB;
+            tv[c] = band_window_ld<VT>(win, e < BS_NB * BS_NB && q <= t && t - q <= b ? (t * b + q) * VS : BAND_NONE);
         }
     };
     band_stage_triangle<VT, AT, NT>(L, w, b, 0, min(BS_NB, n), sT);
@@ -902,7 +947,7 @@ __device__ void band_llt_solve_ahead(const VT *__restrict__ L, int n, int b, AT 
     }
     if (nblk > 1) {
         load_rows(0);
-        band_load_triangle<VT, AT, NT>(L, w, b, BS_NB, min(BS_NB, n - BS_NB), tv);
+        load_triangle(BS_NB);
     }
     __syncthreads();
     for (int blk = 0; blk + 1 < nblk; ++blk) {
@@ -946,7 +991,7 @@ __device__ void band_llt_solve_ahead(const VT *__restrict__ L, int n, int b, AT 
         band_store_triangle<AT, NT>(tv, sT);
         if (blk + 2 < nblk) {   // the next step's rows and triangle
             load_rows(k1);
-            band_load_triangle<VT, AT, NT>(L, w, b, k1 + BS_NB, min(BS_NB, n - k1 - BS_NB), tv);
+            load_triangle(k1 + BS_NB);
         }
         __syncthreads();
         if (tid < 64) {
@@ -959,12 +1004,30 @@ __device__ void band_llt_solve_ahead(const VT *__restrict__ L, int n, int b, AT 
     // cv[s] = L(k0 + s, j) for the thread's first column j = max(0, k0 - b) + tid
     // above the block at k0 (zero outside the band)
     AT cv[BPF];
-    auto load_col = [&](int k0) {
-        const int kb = min(BS_NB, n - k0), j = max(0, k0 - b) + tid;
-        const int smax = min(kb, j + b - k0 + 1);
-        const VT *col = L + int64_t(k0) * w + (j - k0 + b);
+    // entry (k0 + s, j) lies s b + j - (k0 - b) entries after row k0's first;
+    // only the first wavefront's columns end inside the block's rows
+    auto load_col = [&](int k0) __attribute__((always_inline)) {
+        const int64_t at0 = int64_t(k0) * w;
+        const __amdgpu_buffer_rsrc_t win = band_window(L + at0, len - at0);
+        const int wv = __builtin_amdgcn_readfirstlane(tid / 64);
+        int jj = tid + max(0, b - k0);   // j - (k0 - b)
+        int at = jj < b ? jj * VS : BAND_NONE, step = b * VS;
+        // (tests and offsets are formed one by one as the loads go out: no
+        // registers hold them)
+        asm volatile("" : "+v"(jj), "+v"(at), "+s"(step));
+        if (wv == 0) {
 #pragma unroll
-        for (int s = 0; s < BPF; ++s) cv[s] = (j < k0 && s < smax) ? to_acc(band_ld(&col[int64_t(s) * (w - 1)])) : AT(0);
+            for (int s = 0; s < BPF; ++s, at += step) {
+                cv[s] = band_window_ld<VT>(win, s <= jj ? at : BAND_NONE);
+                asm volatile("" : "+v"(at), "+v"(jj) : : "memory");
+            }
+        } else if (wv * 64 < min(b, k0)) {
+#pragma unroll
+            for (int s = 0; s < BPF; ++s, at += step) {
+                cv[s] = band_window_ld<VT>(win, at);
+                asm volatile("" : "+v"(at) : : "memory");
+            }
+        }
     };
     {
         const int k0 = (nblk - 1) * BS_NB, kb = n - k0;
@@ -976,7 +1039,7 @@ __device__ void band_llt_solve_ahead(const VT *__restrict__ L, int n, int b, AT 
         }
         if (nblk > 1) {
             load_col(k0);
-            band_load_triangle<VT, AT, NT>(L, w, b, k0 - BS_NB, BS_NB, tv);
+            load_triangle(k0 - BS_NB);
         }
         __syncthreads();
     }
@@ -987,8 +1050,9 @@ __device__ void band_llt_solve_ahead(const VT *__restrict__ L, int n, int b, AT 
         {
             const int j = jbeg + tid;
             if (j < k0) {
-                const int smax = min(kb, j + b - k0 + 1);
-                const VT *col = L + int64_t(k0) * w + (j - k0 + b);
+                const int64_t at0 = int64_t(k0) * w;
+                const __amdgpu_buffer_rsrc_t win = band_window(L + at0, len - at0);
+                const int jj = j - (k0 - b);
                 // (the block's vector entries: at fixed offsets for a whole
                 // block, clamped to the last row for the last one)
                 auto col_sum = [&](auto yat) {
@@ -1000,7 +1064,7 @@ __device__ void band_llt_solve_ahead(const VT *__restrict__ L, int n, int b, AT 
                         AT u[G];
 #pragma unroll
                         for (int q = 0; q < G; ++q)
-                            u[q] = (g + q < smax) ? to_acc(band_ld(&col[int64_t(g + q) * (w - 1)])) : AT(0);
+                            u[q] = band_window_ld<VT>(win, g + q <= jj ? (jj + (g + q) * b) * VS : BAND_NONE);
 #pragma unroll
                         for (int q = 0; q < G; ++q) acc += u[q] * yat(g + q);
                     }
@@ -1030,7 +1094,7 @@ __device__ void band_llt_solve_ahead(const VT *__restrict__ L, int n, int b, AT 
         band_store_triangle<AT, NT>(tv, sT);
         if (blk > 1) {   // the next step's column and triangle
             load_col(p0);
-            band_load_triangle<VT, AT, NT>(L, w, b, p0 - BS_NB, BS_NB, tv);
+            load_triangle(p0 - BS_NB);
         }
         __syncthreads();
         if (tid < 64) {
