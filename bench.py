@@ -47,12 +47,14 @@ ORDERS = {"natural": 0, "nd": 1, "auto": 2}
 MEASURED_TRAFFIC = {
     ("k_ilu_jacobi", "poisson128^3_P8^3", "fp64"): {"bytes": 270263559, "src": "04585098cbd2f750"},
     ("k_ilu_jacobi", "poisson128^3_P8^3", "fp16"): {"bytes": 203127279, "src": "04585098cbd2f750"},
-    ("k_band_apply", "poisson128^3_P8^3", "fp64"): {"bytes": 14214170851, "src": "af0e9d368f9e553e"},
-    ("k_band_apply", "elasticity48^3", "fp32"): {"bytes": 1623322957, "src": "af0e9d368f9e553e"},
-    ("k_nd_apply", "poisson128^3_P8^3", "fp64"): {"bytes": 5574150050, "src": "a6f6d04cf1931195"},
-    ("k_nd_apply", "poisson128^3_P8^3", "fp16"): {"bytes": 1744098215, "src": "a6f6d04cf1931195"},
+    ("k_band_apply", "poisson128^3_P8^3", "fp64"): {"bytes": 14283936668, "src": "9d43797bed387214"},
+    ("k_band_apply", "elasticity48^3", "fp32"): {"bytes": 1624915856, "src": "9d43797bed387214"},
+    ("k_nd_apply", "poisson128^3_P8^3", "fp64"): {"bytes": 5540125912, "src": "8441bb8b8ebbb218"},
+    ("k_nd_apply", "poisson128^3_P8^3", "fp16"): {"bytes": 1740174265, "src": "8441bb8b8ebbb218"},
     # ILU(1) factors from 3 FastILU sweeps (the traffic does not depend on how the factors were computed)
     ("k_ilu_jacobi_phased", "poisson128^3_P8^3", "fp64"): {"bytes": 449873130, "src": "4e1cfa6c27b7f1c8"},
+    # ILU(2) factors from 3 FastILU sweeps (the entry holds for ILU(2) only)
+    ("k_ilu_jacobi_blocks", "poisson128^3_P8^3", "fp64"): {"bytes": 763049843, "src": "3d3713ecb7f927f1"},
 }
 
 
@@ -310,7 +312,8 @@ def single(kind="poisson", N=None, Pn=None, local="ilu0", prec="fp64", coarse=No
                    + nloc * 12 + n * 20)
     traffic = None
     meas = None
-    if (ilu_level == 0 and factor_sweeps == 0) or (kname == "k_ilu_jacobi_phased" and ilu_level == 1):
+    if ((ilu_level == 0 and factor_sweeps == 0) or (kname == "k_ilu_jacobi_phased" and ilu_level == 1)
+            or (kname == "k_ilu_jacobi_blocks" and ilu_level == 2)):
         meas = MEASURED_TRAFFIC.get((kname, f"poisson{N}^3_P{Pn}^3" if not elastic else f"elasticity{N}^3", prec))
     if meas and kernel_source_hash(kname) == meas["src"]:
         traffic = int(meas["bytes"])
