@@ -48,21 +48,29 @@ __device__ __forceinline__ void wave_lds_fence() {
 
 // x / s, correctly rounded, with y = 1 / s correctly rounded (Markstein: the
 // quotient's remainder is exact in one multiply-add, and adding remainder times
-// y rounds once)
+// y rounds once).  For |x| of at least 2^-968 or zero, where the remainder is a
+// multiple of the smallest subnormal, and quotients in the normal range; below
+// that (entries of a band that decay past 1e-291) the last bit may differ.
 __device__ __forceinline__ double div_by(double x, double s, double y) {
     const double q = x * y;
     return __builtin_fma(__builtin_fma(-s, q, x), y, q);
 }
 
 // 1 / s for s = sqrt(d), correctly rounded: 1 / sqrt(d) from the hardware's
-// estimate to about an ulp beside the square root's own chain, then one
-// correction with s itself
+// estimate to about an ulp beside the square root's own chain, then two
+// corrections with s itself.  The first leaves less than an ulp (the estimate's
+// error, the root's rounding and the square's make up to two, from which one
+// correction misses the rounding for some s); from there the second rounds
+// correctly (Markstein) for every s but those with all mantissa bits set, whose
+// reciprocal lies 2^-53 of itself above a power of two and is the double after it.
 __device__ __forceinline__ double rcp_of_sqrt(double d, double s) {
     double y = __builtin_amdgcn_rsq(d);
     double e = __builtin_fma(-d * y, y, 1.0);
     y = __builtin_fma(y, __builtin_fma(0.375 * e, e, 0.5 * e), y);
-    e = __builtin_fma(-s, y, 1.0);
-    return __builtin_fma(e, y, y);
+    y = __builtin_fma(__builtin_fma(-s, y, 1.0), y, y);
+    y = __builtin_fma(__builtin_fma(-s, y, 1.0), y, y);
+    const bool ones = __double2loint(s) == -1 && (__double2hiint(s) & 0xfffff) == 0xfffff;
+    return __hiloint2double(__double2hiint(y), __double2loint(y) | int(ones));
 }
 
 // Cholesky elimination with 16 pivots by one wavefront, a row per lane: lanes
