@@ -337,8 +337,9 @@ __global__ __launch_bounds__(NT) void k_ilu_jacobi_blocks(
         VT v[KM];
         uint16_t c[KM];
     };
-    // slots past K re-read the last one and are not used; rows outside the
-    // subdomain read its first or last row and are not written
+    // slots past K re-read the last one and are not used; padding slots read
+    // the row itself, which is in the ring (column 0 may have left it); rows
+    // outside the subdomain read its first or last row and are not written
     auto at = [&](int l) { return min(max(l, 0), last); };
     auto load = [&](Row &w, const VT *__restrict__ V, const uint16_t *__restrict__ C, int K, int l) {
         const int64_t e0 = eo + at(l);

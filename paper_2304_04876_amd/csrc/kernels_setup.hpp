@@ -185,26 +185,34 @@ __global__ void k_ilu_pack(const int64_t *__restrict__ ov_ptr, const int64_t *__
     } else {
         dinv[R] = from_double<VT>(0.0);
     }
+    // padding: a zero in the row's own column, so that whichever rows of an
+    // iterate a kernel keeps at hand the padding reads one of them, and an
+    // infinity reaches no row that does not couple to it (rows past the
+    // subdomain: column 0)
+    const uint16_t own = l < ni ? uint16_t(l) : uint16_t(0);
+    const int nl = sl, nu = su;
     for (; sl < KL; ++sl) {
         Lv[sl * ell_rows + R] = from_double<VT>(0.0);
-        Lc[sl * ell_rows + R] = 0;
+        Lc[sl * ell_rows + R] = own;
     }
     for (; su < KU; ++su) {
         Uv[su * ell_rows + R] = from_double<VT>(0.0);
-        Uc[su * ell_rows + R] = 0;
+        Uc[su * ell_rows + R] = own;
     }
     // Cp != nullptr: the row's L then U columns again, two per 32-bit word
     // (low half first), (KL + KU + 1) / 2 words per row, for the
     // register-resident sweeps: the words of a row together (cp_stride 0),
     // or word w of every row at w * cp_stride (each phase of the phased
-    // sweeps then reads only its own words)
+    // sweeps then reads only its own words); padding in column 0, which these
+    // sweeps keep (every row)
     if (Cp) {
         const int cw = (KL + KU + 1) / 2;
         for (int w = 0; w < cw; ++w) {
             uint32_t v = 0;
             for (int h = 0; h < 2; ++h) {
                 const int k = 2 * w + h;
-                const uint32_t c = k < KL ? Lc[k * ell_rows + R] : (k < KL + KU ? Uc[(k - KL) * ell_rows + R] : 0u);
+                const uint32_t c = k < nl ? Lc[k * ell_rows + R]
+                                   : k >= KL && k < KL + nu ? Uc[(k - KL) * ell_rows + R] : 0u;
                 v |= c << (16 * h);
             }
             Cp[cp_stride ? w * cp_stride + R : R * cw + w] = v;
