@@ -35,7 +35,7 @@ namespace gdsw {
 // subtracted once; then one subtraction per earlier column).  With all 256
 // threads on one update or column after another, each between barriers, and
 // rank-one updates through memory, 216 subdomains of 5,632 rows took 50.2 ms;
-// now 5.3 ms.  status[i] = 1 + new local row of a non-positive pivot.
+// now 5.3 ms.  status[i] = 1 + new local row of the first non-positive pivot.
 
 // acc + A B^T-like chain over columns [0, kn) of a column-major panel: D(i, j) +=
 // sum_k (neg ? -x : x)_k(i) y_k(j), x and y rows li of the panel at xr and yr
@@ -110,7 +110,8 @@ __device__ __forceinline__ void nd_panel(double *__restrict__ P, int n, int ld, 
             int bad = 0;
             double ds, dy;
             elim16<true>(a, lane, c0, bad, ds, dy, cw);
-            if (bad && lane == 0) atomicCAS(status, 0, row0 + bad);
+            // (panels of one height fail in any order: the first row of all is kept)
+            if (bad && lane == 0 && atomicCAS(status, 0, row0 + bad) != 0) atomicMin(status, row0 + bad);
             static_for<EB>([&](auto c) {
                 if (c < cw && r < ld && lane >= c) P[int64_t(c0 + c) * ld + r] = lane == c ? ds : a[c];
             });
