@@ -9,7 +9,6 @@
 #include <new>
 #include <stdexcept>
 #include <string>
-#include <system_error>
 #include <thread>
 #include <vector>
 
@@ -1204,7 +1203,7 @@ gdsw_status refactor(gdsw_handle_s *h, const double *val, void *stream) {
         return GDSW_ERR_INVALID_ARG;
     }
     if (!h->factored || !h->dev) {
-        copy_values(h->sym.val.data(), val, h->sym.nnz);
+        std::copy(val, val + h->sym.nnz, h->sym.val.begin());
         return factor(h, stream);
     }
     hipStream_t s = static_cast<hipStream_t>(stream);
@@ -1219,19 +1218,20 @@ gdsw_status refactor(gdsw_handle_s *h, const double *val, void *stream) {
         ~Copier() { if (t.joinable()) t.join(); }
     } copier;
     try {
-        copier.t = std::thread([&S, val] { copy_values(S.val.data(), val, S.nnz); });
-    } catch (const std::system_error &) {
-        copy_values(S.val.data(), val, S.nnz);
+        copier.t = std::thread([&S, val] { std::copy(val, val + S.nnz, S.val.begin()); });
+    } catch (const std::exception &) {   // (no thread, or no memory for one)
+        std::copy(val, val + S.nnz, S.val.begin());
     }
     try {
         D.keep_setup = true;
+        // (the caller's values, pinned ones too, are not read after a return)
         HIPCHK(hipMemcpyAsync(D.val, val, sizeof(double) * size_t(S.nnz), hipMemcpyHostToDevice, s));
+        HIPCHK(hipStreamSynchronize(s));
         // the sliced ELL copy from the CSR values, on the device (building it
         // on the host and sending it took 25 ms at 128^3)
         hipLaunchKernelGGL(k_sell_values, dim3(nblocks(S.n, SELL_C)), dim3(SELL_C), 0, s, D.rowptr, D.val, D.sell.off,
                            const_cast<double *>(D.sell.val), int(S.n));
         HIPCHK(hipGetLastError());
-        HIPCHK(hipStreamSynchronize(s));   // (the caller's values have been read)
         factor_local(h, s);
         coarse_numeric(h, s);
         HIPCHK(hipStreamSynchronize(s));
