@@ -563,6 +563,20 @@ static void check_status(Device &D, int *d_status, int count, hipStream_t s, con
 // columns of that height, the limit the callers' sizes are checked against).
 static int chol_max_band(const Device &D) { return std::max(1, int((D.max_lds / sizeof(double) - 16 * 18) / 17)); }
 
+// Band Cholesky of np matrices of bandwidth up to max_b: more than three of
+// them for each compute unit (k_band_chol runs one there at a time) and narrow
+// take k_band_chol_small; between 512 and 1,000 matrices and between bandwidths
+// 45 and 60 the two change places (times at the kernel).
+static void launch_band_chol(const Device &D, int np, int max_b, double *band, const int64_t *off, const int32_t *bw,
+                             const int64_t *rptr, int *d_status, hipStream_t s) {
+    if (np > 3 * D.n_cu && max_b <= 48)
+        hipLaunchKernelGGL(k_band_chol_small<128>, dim3(np), dim3(128), band_chol_small_lds(max_b), s, band, off, bw,
+                           rptr, d_status);
+    else
+        hipLaunchKernelGGL(k_band_chol<512>, dim3(np), dim3(512), 0, s, band, off, bw, rptr, d_status);
+    HIPCHK(hipGetLastError());
+}
+
 // Replaces the 64x64 diagonal blocks of the band factors of every subdomain
 // whose band holds whole triangles by their inverses (k_band_invert_diag);
 // rows_h: host row offsets of the subdomains, bw_h: host bandwidths.
@@ -800,9 +814,7 @@ static void factor_band(gdsw_handle_s *h, int *d_status, hipStream_t s) {
         if (!D.queue) D.queue = D.alloc<int>(2 * QUEUE_HALF);
         if (chol_max_band(D) < S.max_bw)
             throw DevError{GDSW_ERR_INVALID_ARG, "local bandwidth too large for the banded Cholesky"};
-        hipLaunchKernelGGL(k_band_chol<512>, dim3(S.np), dim3(512), 0, s, band64, D.band_off, D.bw, D.ov_ptr,
-                           d_status);
-        HIPCHK(hipGetLastError());
+        launch_band_chol(D, S.np, S.max_bw, band64, D.band_off, D.bw, D.ov_ptr, d_status, s);
         check_status(D, d_status, S.np, s, "banded Cholesky");
         D.band_kinds = invert_diagonal_blocks(D, band64, D.band_off, D.bw, D.ov_ptr, S.ov_ptr, S.bw, S.np,
                                               ST_BP_LOCAL, s, &S.band_off);
@@ -1004,8 +1016,7 @@ static void coarse_numeric(gdsw_handle_s *h, hipStream_t s) {
         hipLaunchKernelGGL(k_gather_vals, dim3(nblocks(ne, 256, 65536)), dim3(256), 0, s, D.val, d_src, d_dst, iband,
                            ne, (const double *)nullptr, D.arow, D.col);
         if (chol_max_band(D) < S.max_ibw) throw DevError{GDSW_ERR_INVALID_ARG, "interior bandwidth too large"};
-        hipLaunchKernelGGL(k_band_chol<512>, dim3(S.np), dim3(512), 0, s, iband, d_ioff, d_ibw, d_int_ptr, d_status);
-        HIPCHK(hipGetLastError());
+        launch_band_chol(D, S.np, S.max_ibw, iband, d_ioff, d_ibw, d_int_ptr, d_status, s);
         check_status(D, d_status, S.np, s, "interior Cholesky");
         const int ikinds = invert_diagonal_blocks(D, iband, d_ioff, d_ibw, d_int_ptr, S.int_ptr, S.ibw, S.np,
                                                   ST_BP_INT, s);

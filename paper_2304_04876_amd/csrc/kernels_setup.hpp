@@ -586,6 +586,108 @@ __global__ __launch_bounds__(NT) void k_band_chol(double *__restrict__ band, con
     }
 }
 
+// The same factor, bit for bit, for many narrow bands: the right-looking loop
+// itself, panels of 16 columns, multiply-adds, the window below a panel updated
+// in memory.  k_band_chol's 141 KB of LDS hold one workgroup per compute unit,
+// whatever the band; here sixteen of 128 threads fit one, and a band of a few
+// panels has no long chain to hide.  LDS: band_chol_small_lds(largest band).
+// Per launch against k_band_chol: 4,096 bands of 160 rows (bandwidth 32) 537
+// against 1,029 us, 8,000 of 81 (21) 420 against 1,162, 1,000 of 275 (45) 422
+// against 473; 512 of 275 374 against 247, 1,000 of 432 (60) 806 against 757.
+constexpr int CH_NB = 16;
+constexpr int CH_LD = CH_NB + 1;   // padded LDS row stride (bank spread)
+__host__ __device__ constexpr size_t band_chol_small_lds(int b) {
+    return sizeof(double) * (CH_NB * CH_LD + CH_NB + size_t(b < 1 ? 1 : b) * CH_LD);
+}
+
+template <int NT>
+__global__ __launch_bounds__(NT) void k_band_chol_small(double *__restrict__ band, const int64_t *__restrict__ off,
+                                                        const int32_t *__restrict__ bwid,
+                                                        const int64_t *__restrict__ rptr, int *__restrict__ status) {
+    extern __shared__ double smem[];
+    const int i = blockIdx.x;
+    if (off[i + 1] == off[i]) return;   // no band (empty, or a supernodal subdomain)
+    const int n = int(rptr[i + 1] - rptr[i]);
+    const int b = bwid[i];
+    const int64_t w = b + 1;
+    double *L = band + off[i];
+    double *sD = smem;                 // CH_NB x CH_LD
+    double *sdg = sD + CH_NB * CH_LD;  // CH_NB
+    double *sP = sdg + CH_NB;          // b x CH_LD
+    const int tid = threadIdx.x;
+    for (int k0 = 0; k0 < n; k0 += CH_NB) {
+        const int kb = min(CH_NB, n - k0);
+        // (a) diagonal block, left-looking by columns
+        for (int e = tid; e < CH_NB * CH_NB; e += NT) {
+            const int t = e / CH_NB, s = e % CH_NB;
+            double v = 0.0;
+            if (t < kb && s <= t && t - s <= b) v = L[int64_t(k0 + t) * w + (s - t + b)];
+            sD[t * CH_LD + s] = v;
+        }
+        __syncthreads();
+        for (int j = 0; j < kb; ++j) {
+            const int t = j + tid;
+            if (t < kb) {
+                double v = sD[t * CH_LD + j];
+                for (int s = 0; s < j; ++s) v -= sD[t * CH_LD + s] * sD[j * CH_LD + s];
+                if (t == j) {
+                    if (!(v > 0.0)) {
+                        atomicCAS(status + i, 0, 1 + k0 + j);
+                        v = 1.0;
+                    }
+                    sdg[j] = sqrt(v);
+                } else {
+                    sD[t * CH_LD + j] = v;
+                }
+            }
+            __syncthreads();
+            if (t > j && t < kb) sD[t * CH_LD + j] /= sdg[j];
+            __syncthreads();
+        }
+        for (int e = tid; e < kb * kb; e += NT) {
+            const int t = e / kb, s = e % kb;
+            if (s <= t && t - s <= b)
+                L[int64_t(k0 + t) * w + (s - t + b)] = (s == t) ? 1.0 / sdg[t] : sD[t * CH_LD + s];
+        }
+        // (b) rows below the diagonal block: P <- P L_D^{-T}
+        const int rbeg = k0 + kb;
+        const int rend = min(n, k0 + kb + b);
+        const int m = max(0, rend - rbeg);
+        for (int q = tid; q < m; q += NT) {
+            const int r = rbeg + q;
+            const int s0 = max(0, r - b - k0);
+            double x[CH_NB];
+#pragma unroll
+            for (int s = 0; s < CH_NB; ++s) {
+                double v = 0.0;
+                if (s >= s0 && s < kb) {
+                    v = L[int64_t(r) * w + (k0 + s - r + b)];
+                    for (int t = 0; t < s; ++t) v -= x[t] * sD[s * CH_LD + t];   // x[t] = 0 for t < s0
+                    v /= sdg[s];
+                }
+                x[s] = v;
+            }
+#pragma unroll
+            for (int s = 0; s < CH_NB; ++s) {
+                sP[q * CH_LD + s] = x[s];
+                if (s >= s0 && s < kb) L[int64_t(r) * w + (k0 + s - r + b)] = x[s];
+            }
+        }
+        __syncthreads();
+        // (c) trailing window: A(r, c) -= P(r,:) . P(c,:), c <= r
+        for (int e = tid; e < m * m; e += NT) {
+            const int rq = e / m, cq = e % m;
+            if (cq > rq) continue;
+            double acc = 0.0;
+#pragma unroll
+            for (int s = 0; s < CH_NB; ++s) acc += sP[rq * CH_LD + s] * sP[cq * CH_LD + s];
+            const int r = rbeg + rq, c = rbeg + cq;
+            L[int64_t(r) * w + (c - r + b)] -= acc;
+        }
+        __syncthreads();
+    }
+}
+
 // Partitioned inverse of the diagonal blocks of a band Cholesky factor
 // (FP64, before any cast): the 64x64 diagonal block L_kk of rows k0 ..
 // k0+kb-1 is replaced in place by X = L_kk^{-1} (lower triangular; its
