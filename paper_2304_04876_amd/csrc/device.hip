@@ -563,13 +563,13 @@ static void check_status(Device &D, int *d_status, int count, hipStream_t s, con
 // columns of that height, the limit the callers' sizes are checked against).
 static int chol_max_band(const Device &D) { return std::max(1, int((D.max_lds / sizeof(double) - 16 * 18) / 17)); }
 
-// Band Cholesky of np matrices of bandwidth up to max_b: more than three of
-// them for each compute unit (k_band_chol runs one there at a time) and narrow
-// take k_band_chol_small; between 512 and 1,000 matrices and between bandwidths
+// Band Cholesky of the np subdomains, `count` of them with a band, of bandwidth
+// up to max_b: more than three for each compute unit (k_band_chol runs one there
+// at a time) and narrow take k_band_chol_small; between 512 and 1,000 matrices and between bandwidths
 // 45 and 60 the two change places (times at the kernel).
-static void launch_band_chol(const Device &D, int np, int max_b, double *band, const int64_t *off, const int32_t *bw,
-                             const int64_t *rptr, int *d_status, hipStream_t s) {
-    if (np > 3 * D.n_cu && max_b <= 48)
+static void launch_band_chol(const Device &D, int np, int64_t count, int max_b, double *band, const int64_t *off,
+                             const int32_t *bw, const int64_t *rptr, int *d_status, hipStream_t s) {
+    if (count > 3 * D.n_cu && max_b <= 48)
         hipLaunchKernelGGL(k_band_chol_small<128>, dim3(np), dim3(128), band_chol_small_lds(max_b), s, band, off, bw,
                            rptr, d_status);
     else
@@ -660,9 +660,23 @@ static void factor_nd(gdsw_handle_s *h, int *d_status, hipStream_t s) {
     int32_t *d_up_n1 = D.setup_upload(N.up_n1, s);
     int64_t *d_up_rel = D.setup_upload(N.up_rel, s);
     int32_t *d_rel = D.setup_upload(N.rel, s);
-    hipLaunchKernelGGL(k_nd_factor<1024>, dim3(S.np), dim3(1024), 0, s, P64, D.nd_sn_ptr, D.nd_first, D.nd_ncol,
-                       D.nd_nrow, D.nd_voff, D.nd_st_ptr, d_up_ptr, d_up_k, d_up_s0, d_up_n1, d_up_rel, d_rel,
-                       D.ov_ptr, D.nd_row_sn, D.nd_lv_base, D.nd_lv_ptr, d_status);
+    // threads per subdomain: as many wavefronts as its heights have work for,
+    // unless more subdomains than compute units share the device and are small
+    // (per launch, 1,024 / 256 / 128 threads: 216 of 1,600 rows 1.19 / 1.37 / 2.21
+    // ms; 512 of 432 rows 524 / 307 / 400 us, of 5,632 11.4 / 12.2 / 18.4 ms;
+    // 1,000 of 432 1,023 / 579 / 458 us; 8,000 of 81 2.24 / 0.68 / 0.42 ms)
+    const auto factor = [&](auto nt) {
+        hipLaunchKernelGGL(k_nd_factor<decltype(nt)::value>, dim3(S.np), dim3(decltype(nt)::value), 0, s, P64,
+                           D.nd_sn_ptr, D.nd_first, D.nd_ncol, D.nd_nrow, D.nd_voff, D.nd_st_ptr, d_up_ptr, d_up_k,
+                           d_up_s0, d_up_n1, d_up_rel, d_rel, D.ov_ptr, D.nd_row_sn, D.nd_lv_base, D.nd_lv_ptr, d_status);
+    };
+    const int64_t nnd = std::count(S.nd_mask.begin(), S.nd_mask.end(), uint8_t(1));
+    if (nnd <= D.n_cu || D.nd_max_ni > 2048)
+        factor(std::integral_constant<int, 1024>{});
+    else if (nnd <= 3 * D.n_cu)
+        factor(std::integral_constant<int, 256>{});
+    else
+        factor(std::integral_constant<int, 128>{});
     HIPCHK(hipGetLastError());
     check_status(D, d_status, S.np, s, "supernodal Cholesky");
     const size_t lds = sizeof(double) * size_t(std::max(N.max_ncol, 1));
@@ -814,7 +828,8 @@ static void factor_band(gdsw_handle_s *h, int *d_status, hipStream_t s) {
         if (!D.queue) D.queue = D.alloc<int>(2 * QUEUE_HALF);
         if (chol_max_band(D) < S.max_bw)
             throw DevError{GDSW_ERR_INVALID_ARG, "local bandwidth too large for the banded Cholesky"};
-        launch_band_chol(D, S.np, S.max_bw, band64, D.band_off, D.bw, D.ov_ptr, d_status, s);
+        launch_band_chol(D, S.np, std::count(S.nd_mask.begin(), S.nd_mask.end(), uint8_t(0)), S.max_bw, band64,
+                         D.band_off, D.bw, D.ov_ptr, d_status, s);
         check_status(D, d_status, S.np, s, "banded Cholesky");
         D.band_kinds = invert_diagonal_blocks(D, band64, D.band_off, D.bw, D.ov_ptr, S.ov_ptr, S.bw, S.np,
                                               ST_BP_LOCAL, s, &S.band_off);
@@ -1016,7 +1031,7 @@ static void coarse_numeric(gdsw_handle_s *h, hipStream_t s) {
         hipLaunchKernelGGL(k_gather_vals, dim3(nblocks(ne, 256, 65536)), dim3(256), 0, s, D.val, d_src, d_dst, iband,
                            ne, (const double *)nullptr, D.arow, D.col);
         if (chol_max_band(D) < S.max_ibw) throw DevError{GDSW_ERR_INVALID_ARG, "interior bandwidth too large"};
-        launch_band_chol(D, S.np, S.max_ibw, iband, d_ioff, d_ibw, d_int_ptr, d_status, s);
+        launch_band_chol(D, S.np, S.np, S.max_ibw, iband, d_ioff, d_ibw, d_int_ptr, d_status, s);
         check_status(D, d_status, S.np, s, "interior Cholesky");
         const int ikinds = invert_diagonal_blocks(D, iband, d_ioff, d_ibw, d_int_ptr, S.int_ptr, S.ibw, S.np,
                                                   ST_BP_INT, s);

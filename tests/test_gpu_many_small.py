@@ -35,6 +35,13 @@ def test_band_cholesky_of_many(N):
     _copies_equal_alone(N, 769, B.ORDER_NATURAL)
 
 
+# leaves alone up to several heights, with the 128 and the 256 threads that more
+# than three and one to three subdomains per compute unit take
+@pytest.mark.parametrize("N,copies", [(2, 769), (3, 769), (6, 769), (9, 769), (3, 300), (9, 300), (12, 257)])
+def test_supernodal_cholesky_of_many(N, copies):
+    _copies_equal_alone(N, copies, B.ORDER_ND)
+
+
 def test_failing_row_of_one_of_many():
     pr = P.poisson3d(5, 1)
     A = sp.block_diag([pr.A] * 800, format="csr")
