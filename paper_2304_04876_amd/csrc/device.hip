@@ -1358,11 +1358,77 @@ static bool launch_ilu_blocks(const Symbolic &S, Device &D, const double *r, con
     }
 }
 
+// Factors with more slots than the register-resident kernels take, with the
+// first 6 slots of each row held in registers (4 with FP64 entries for more than
+// 4,096 rows a workgroup, the register budget) and the rest streamed (512
+// threads with up to 11 rows each, or 1024 with up to 6, 4 for FP64).
+// any = false: only where this is ahead of the sweeps by blocks of rows, which
+// pay a load's latency per block and are ahead when the factors' later slots
+// would be read again on several sweeps, or from memory instead of the caches
+// (200 MB).  With two sweeps no slot is read again: this form, but for FP64 ILU(2)
+// and ILU(3) factors past the caches or with idle rows (R rows a thread, a
+// subdomain needing fewer than 4/5 of them).  With three: for few slots to
+// read again, FP64 up to 12 a triangle (or every thread's rows full), FP32, and
+// 16-bit entries from 13 on.
+// Measured (us, this form / by blocks; 27, 125 and 512 subdomains of 5,632 rows,
+// 64 of 2,592): ILU(2) FP64 two sweeps 41 / 55, 45 / 60, 155 / 146, 32 / 33,
+// three 57 / 62, 65 / 67, 203 / 151, 45 / 37; ILU(3) FP32 two sweeps 38 / 54,
+// 45 / 62, 171 / 175, 25 / 32, three 55 / 63, 66 / 70, 231 / 186, 37 / 36; five
+// sweeps of ILU(2) FP64 89 / 78.
+template <typename VT, int NT>
+static bool launch_ilu_hold(const Symbolic &S, Device &D, const double *r, const Skip &sk, hipStream_t s,
+                            const Device::SizeClass &c, bool any) {
+    if constexpr (NT != 512 && NT != 1024) {
+        return false;
+    } else {
+        const int sweeps = S.opt.jacobi_sweeps, K = std::max(D.KLp, D.KUp);
+        if (sweeps < 2 || !D.Lc || !D.Uc || D.KLp < 2 || D.KUp < 2) return false;
+        using AT = typename AccOf<VT>::type;
+        constexpr bool f64 = std::is_same<VT, double>::value;
+        const size_t lds = 3 * sizeof(AT) * size_t(std::max(c.max_ni, 1));
+        if (lds > D.max_lds) return false;
+        const int need = (c.max_ni + NT - 1) / NT;
+        const int nb = c.end - c.begin;
+        const Skip kc = class_skip(D, sk, c);
+        const bool cached = D.local_entries * int64_t(sizeof(VT) + 2) <= 200000000;
+        const auto ahead = [&](int R) {
+            const bool filled = 5 * need >= 4 * R;
+            if (sweeps == 2) return !f64 || (K <= 12 ? filled && cached : filled || cached);
+            return sweeps == 3 && filled && cached && (f64 ? K <= 12 || need == R : sizeof(VT) == 4 || K > 12);
+        };
+#define GDSW_ILU_HOLD(RR)                                                                                     \
+        if (need <= RR) {                                                                                     \
+            if (!any && !ahead(RR)) return false;                                                             \
+            hipLaunchKernelGGL((k_ilu_jacobi_hold<NT, RR, (f64 && RR * NT > 4096) ? 4 : 6, VT>), dim3(nb, D.ns), \
+                               dim3(NT), lds, s, r,                                                           \
+                               D.ov_idx, D.ov_ptr, D.ell_off, S.ell_rows, D.KLp, D.KUp, (const VT *)D.Lv,     \
+                               D.Lc, (const VT *)D.Uv, D.Uc, (const VT *)D.dinv, D.dscale,                    \
+                               sweeps, D.zloc, c.max_ni, kc);                                                 \
+            return true;                                                                                      \
+        }
+        if constexpr (NT == 512) {
+            GDSW_ILU_HOLD(4)
+            GDSW_ILU_HOLD(8)
+            GDSW_ILU_HOLD(11)
+        } else {
+            GDSW_ILU_HOLD(2)
+            GDSW_ILU_HOLD(4)
+            if constexpr (!f64) { GDSW_ILU_HOLD(6) }   // (FP64 at 6 rows a thread spills)
+        }
+#undef GDSW_ILU_HOLD
+        return false;
+    }
+}
+
 template <typename VT, int NT>
 static bool launch_ilu_regs(const Symbolic &S, Device &D, const double *r, const Skip &sk, hipStream_t s,
                             const Device::SizeClass &c) {
-    // more slots than the phased kernel holds: by blocks of rows
-    if (D.KLp > ILU_KL2 || D.KUp > ILU_KU2) return launch_ilu_blocks<VT, NT>(S, D, r, sk, s, c);
+    // more slots than the phased kernel holds: the first ones held where that is
+    // ahead, else by blocks of rows, else (more than 24 slots, as elasticity has,
+    // or rings past LDS) the first ones held
+    if (D.KLp > ILU_KL2 || D.KUp > ILU_KU2)
+        return launch_ilu_hold<VT, NT>(S, D, r, sk, s, c, false) || launch_ilu_blocks<VT, NT>(S, D, r, sk, s, c) ||
+               launch_ilu_hold<VT, NT>(S, D, r, sk, s, c, true);
     // (one sweep per triangle needs no factor entries: the streaming kernel)
     if (!D.Cp || S.opt.jacobi_sweeps < 2) return false;
     if (D.KLp == ILU_KL2 && D.KUp == ILU_KU2)
