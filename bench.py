@@ -95,6 +95,23 @@ def log(*a):
 GOLD = os.path.join(ROOT, "tests", "golden")
 
 
+def ilu_kernel_name(elastic, ilu_level, prec, variant, rows):
+    """The ILU kernel of a launch configuration for subdomains of up to `rows`
+    rows, five sweeps.  7-point stencil: ILU(0) holds every entry in registers,
+    ILU(1) (6 + 6 slots) L and U one after the other, both while 512 threads take
+    at most 11 rows each (1,024: 8, FP64 4); ILU(2), ILU(3) and larger
+    subdomains go by blocks of rows.  More than 24 slots a triangle (elasticity,
+    ILU(4)): the first ones held."""
+    if variant not in (0, 1):
+        return "k_ilu_jacobi_generic"
+    if elastic or ilu_level > 3:
+        return "k_ilu_jacobi_hold"
+    most = 512 * 11 if variant == 0 else 1024 * (4 if prec == "fp64" else 8)
+    if rows > most:
+        return "k_ilu_jacobi_blocks"
+    return {0: "k_ilu_jacobi", 1: "k_ilu_jacobi_phased"}.get(ilu_level, "k_ilu_jacobi_blocks")
+
+
 def single(kind="poisson", N=None, Pn=None, local="ilu0", prec="fp64", coarse=None, gmres="single_reduce",
            ilu_level=0, factor_sweeps=0, graphs=False, steps=10, warmup=2, kernel_reps=50, autotune=True,
            with_graph_apply=True, order="natural", element_sharing=False):
@@ -290,13 +307,7 @@ def single(kind="poisson", N=None, Pn=None, local="ilu0", prec="fp64", coarse=No
     # restriction index (4 B), the gathered r (8 B), the local result (8 B)
     alg_bytes = info["local_solve_bytes"]
     if local == "ilu0":
-        if info["local_variant"] in (0, 1):
-            # ILU(0): every entry in registers; ILU(1) (6 + 6 slots): L and
-            # U entries in registers one after the other; ILU(2) and up: by
-            # blocks of rows
-            kname = {0: "k_ilu_jacobi", 1: "k_ilu_jacobi_phased"}.get(ilu_level, "k_ilu_jacobi_blocks")
-        else:
-            kname = "k_ilu_jacobi_generic"
+        kname = ilu_kernel_name(elastic, ilu_level, prec, info["local_variant"], info["max_local_rows"])
     elif info["nd_subdomains"] == pr.n_parts:
         kname = "k_nd_apply"
     elif info["nd_subdomains"] == 0:
