@@ -771,8 +771,12 @@ static void factor_local(gdsw_handle_s *h, hipStream_t s) {
             case GDSW_BF16: pack_ilu<bf16>(h, d_lrowptr, d_lcol, d_ldiag, d_lval, s); break;
             default: pack_ilu<fp16>(h, d_lrowptr, d_lcol, d_ldiag, d_lval, s); break;
         }
-        // subdomains whose three sweep vectors do not fit in LDS (and that the
-        // register-resident kernel does not cover) keep them in global memory
+        // subdomains whose three sweep vectors do not fit in LDS keep them in
+        // global memory in the streaming sweeps.  The fixed rule takes another
+        // form for most of them, but gdsw_set_launch and the tuner may choose
+        // the streaming one at any time, and an apply allocates nothing: so the
+        // memory is there (and counted by the allocation-free apply) for every
+        // such handle
         {
             const size_t asz = prec == GDSW_FP64 ? 8 : 4;
             if (3 * asz * size_t(S.max_ni) > D.max_lds && !D.sweep_buf) {
@@ -1592,10 +1596,14 @@ static bool launch_local_variant(const Symbolic &S, Device &D, int v, const doub
 }
 
 // Every size class in the configuration tuned for it, else the handle's
-// (gdsw_set_launch / gdsw_autotune), else the fixed rule: register-resident
-// sweeps when they fit (FP64: 512 threads, reduced precision: 1024), else
-// streaming; exact solves with 1024 threads where every subdomain gets a
-// compute unit of its own, else 512.
+// (gdsw_set_launch / gdsw_autotune), else the fixed rule: sweeps that read the
+// factors once when they fit, else streaming; exact solves with 1024 threads
+// where every subdomain of the class gets a compute unit of its own, else 512.
+// The sweeps take 512 threads in FP64 and 1024 in reduced precision: the
+// register-resident forms hold twice the rows a thread there, and by blocks of
+// rows 27 subdomains of 5,632 rows take (512 / 1024 threads, us, four sweeps)
+// ILU(2) FP64 70 / 62, ILU(3) FP64 116 / 146 (its entries spill), ILU(2) FP32 57 /
+// 46, ILU(3) FP32 86 / 71, ILU(3) FP16 77 / 70.
 template <typename VT>
 static void launch_local_class(const Symbolic &S, Device &D, const double *r, const Skip &sk, hipStream_t s,
                                const Device::SizeClass &c) {
@@ -1607,7 +1615,10 @@ static void launch_local_class(const Symbolic &S, Device &D, const double *r, co
     // at most one exact solve per compute unit: 1,024 threads each (band: 8
     // subdomains of 1,331 rows FP64 224 -> 168 us per launch against 512, 216 of
     // 2,700 FP32 521 -> 375; supernodal: 216 of 5,632 FP64 871 -> 689; with 512
-    // subdomains, two per unit, 512 threads win: 1.33 against 1.43 ms)
+    // subdomains, two per unit, 512 threads win: 1.33 against 1.43 ms).  Counted in
+    // the class, though the classes of a split run at once: 216 of 5,632 rows
+    // beside 512 of 896 take, with 512 threads for both and by this rule, 2.10 and
+    // 1.36 ms (band FP64), 0.90 and 0.75 ms (supernodal)
     const bool few = int64_t(c.end - c.begin) * D.ns <= D.n_cu;
     const int *order = ilu ? (std::is_same<VT, double>::value ? ilu_order_f64 : ilu_order_lo)
                            : few ? band_order_few : band_order;

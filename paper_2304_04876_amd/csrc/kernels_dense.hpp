@@ -1,6 +1,7 @@
 // Small dense FP64 pieces of the numerical setup's factorisations, one
 // wavefront each: sums by matrix instructions, the elimination of 16 columns.
-// All of them round like the scalar loops they stand for.
+// All of them round like the scalar loops they stand for (quotients: in the
+// range given at div_by).
 #pragma once
 
 #include <type_traits>

@@ -30,12 +30,16 @@ namespace gdsw {
 //       matrix instructions, 64 list entries are looked at together;
 //   (2) the dense Cholesky of the panels by blocks of 16 columns (nd_panel),
 //       one panel per wavefront, or where a height has few supernodes (the
-//       large ones) the whole workgroup on one after the other.
+//       large ones) the whole workgroup on one after the other.  Few: fewer
+//       than half the wavefronts.  With 16 of them, fewer than 2 / 4 / 8 / 16
+//       supernodes: 216 subdomains of 5,632 rows 5.32 / 5.33 / 5.37 / 5.68 ms, 27
+//       of elasticity with 3,000 rows 12.9 / 9.3 / 8.9 / 9.1, 8 of 1,300 rows
+//       0.70 / 0.74 / 0.79 / 0.86.
 // Every value is rounded as by the scalar loops (per update one ascending sum,
 // subtracted once; then one subtraction per earlier column).  With all 256
 // threads on one update or column after another, each between barriers, and
 // rank-one updates through memory, 216 subdomains of 5,632 rows took 50.2 ms;
-// now 5.3 ms.  status[i] = 1 + new local row of the first non-positive pivot.
+// now 5.3 ms (with 1,024 threads, 128 registers each, of which 38 spill).  status[i] = 1 + new local row of the first non-positive pivot.
 
 // acc + A B^T-like chain over columns [0, kn) of a column-major panel: D(i, j) +=
 // sum_k (neg ? -x : x)_k(i) y_k(j), x and y rows li of the panel at xr and yr

@@ -249,8 +249,8 @@ __global__ void k_ilu_pack(const int64_t *__restrict__ ov_ptr, const int64_t *__
 // 18,000 beside the first blocks' 33,000, elimination of the rows 12,000), one
 // workgroup per compute unit.  Against a right-looking loop with scalar
 // multiply-adds and window updates through memory: 512 matrices of 3,375 rows
-// and band 225 33.1 -> 7.1 ms, 27 of 3,000 and 335 22.5 -> 3.7 ms.  status[i] =
-// 1 + row of the first non-positive pivot.
+// and band 225 33.1 -> 8.0 ms, 27 of 3,000 and 335 28.2 -> 3.6 ms (45 of the 256
+// registers a lane spill).  status[i] = 1 + row of the first non-positive pivot.
 constexpr int DB = 32, DB_LD = DB + 1;   // panel width, padded LDS row stride (bank spread)
 constexpr int CH_ST = 64 * 16;           // a wavefront's chunk: 64 rows of 16 columns
 
@@ -702,7 +702,7 @@ __global__ __launch_bounds__(NT) void k_band_chol_small(double *__restrict__ ban
 // the same way from those sums.  Every value is the forward substitution's, bit
 // for bit: -(1/L_tt) sum_{c <= s < t} L(t, s) X(s, c) in ascending s.  (Both
 // triangles and the inverse in LDS, one value at a time per lane, held two
-// wavefronts per compute unit: 4.07 ms for 27,136 blocks; now 0.9 ms.)
+// wavefronts per compute unit: 4.07 ms for 27,136 blocks; now 1.3 ms.)
 constexpr int BS_NB_INV = 64;
 
 // forward substitution with a 32x32 triangle (T: column j at LD j, reciprocal
@@ -1010,8 +1010,8 @@ __device__ void band_llt_solve_ahead(const VT *__restrict__ L, int n, int b, AT 
     constexpr int RB = F64 ? 2 : 4;      // forward: row groups per pass past the held ones
     // backward: rows of the thread's first column held (FP32 all 64 of a block:
     // 375 -> 365 us on 216 subdomains of 2,700 rows against 32, 400 -> 389 on
-    // 48^3 elasticity; FP64 32, the registers' limit: 154 -> 139 on 8 of 1,331
-    // rows against 16)
+    // 48^3 elasticity; FP64 32, 154 -> 139 on 8 of 1,331 rows against 16: three
+    // or four registers past what 1,024 threads have, which spill)
     constexpr int BPF = F64 ? 32 : 64;
     constexpr int G = F64 ? 8 : 32;      // backward: loads per group past the held rows
     const int64_t w = b + 1;
