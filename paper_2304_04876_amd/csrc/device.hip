@@ -1228,14 +1228,17 @@ gdsw_status factor(gdsw_handle_s *h, void *stream) {
 // handle is left unfactored (a later refactor or factor starts afresh).
 gdsw_status refactor(gdsw_handle_s *h, const double *val, void *stream) {
     if (!val) return GDSW_ERR_INVALID_ARG;
-    if (!all_finite(val, h->sym.nnz)) {
+    const auto refused = [h] {
         h->err = "non-finite matrix value";
         return GDSW_ERR_INVALID_ARG;
-    }
-    if (!h->factored || !h->dev) {
+    };
+    // the host's own check and copy, where no device has checked
+    const auto take_values = [h, val] {
+        if (!std::all_of(val, val + h->sym.nnz, [](double v) { return std::isfinite(v); })) return false;
         std::copy(val, val + h->sym.nnz, h->sym.val.begin());
-        return factor(h, stream);
-    }
+        return true;
+    };
+    if (!h->factored || !h->dev) return take_values() ? factor(h, stream) : refused();
     hipStream_t s = static_cast<hipStream_t>(stream);
     auto t0 = std::chrono::steady_clock::now();
     Symbolic &S = h->sym;
@@ -1247,16 +1250,28 @@ gdsw_status refactor(gdsw_handle_s *h, const double *val, void *stream) {
         std::thread t;
         ~Copier() { if (t.joinable()) t.join(); }
     } copier;
-    try {
-        copier.t = std::thread([&S, val] { std::copy(val, val + S.nnz, S.val.begin()); });
-    } catch (const std::exception &) {   // (no thread, or no memory for one)
-        std::copy(val, val + S.nnz, S.val.begin());
-    }
+    bool checked = false;
     try {
         D.keep_setup = true;
         // (the caller's values, pinned ones too, are not read after a return)
         HIPCHK(hipMemcpyAsync(D.val, val, sizeof(double) * size_t(S.nnz), hipMemcpyHostToDevice, s));
+        // Non-finite values are refused before anything else is touched: D.val
+        // is read by the setup alone, which starts by writing it.  Checked on
+        // the device: 14.6 M values took 0.5 ms in 16 host threads, which a
+        // process may not be able to start
+        int *d_bad = D.setup_scratch<int>(ST_STATUS, S.np), bad = 0;
+        HIPCHK(hipMemsetAsync(d_bad, 0, sizeof(int), s));
+        hipLaunchKernelGGL(k_check_finite, dim3(nblocks(S.nnz, 256, 4096)), dim3(256), 0, s, D.val, S.nnz, d_bad);
+        HIPCHK(hipGetLastError());
+        HIPCHK(hipMemcpyAsync(&bad, d_bad, sizeof(int), hipMemcpyDeviceToHost, s));
         HIPCHK(hipStreamSynchronize(s));
+        if (bad) return refused();
+        checked = true;
+        try {
+            copier.t = std::thread([&S, val] { std::copy(val, val + S.nnz, S.val.begin()); });
+        } catch (const std::exception &) {   // (no thread, or no memory for one)
+            std::copy(val, val + S.nnz, S.val.begin());
+        }
         // the sliced ELL copy from the CSR values, on the device (building it
         // on the host and sending it took 25 ms at 128^3)
         hipLaunchKernelGGL(k_sell_values, dim3(nblocks(S.n, SELL_C)), dim3(SELL_C), 0, s, D.rowptr, D.val, D.sell.off,
@@ -1266,10 +1281,12 @@ gdsw_status refactor(gdsw_handle_s *h, const double *val, void *stream) {
         coarse_numeric(h, s);
         HIPCHK(hipStreamSynchronize(s));
     } catch (const DevError &e) {
+        if (!checked && !take_values()) return refused();
         h->err = e.msg;
         h->factored = false;
         return e.st;
     } catch (const std::bad_alloc &) {
+        if (!checked && !take_values()) return refused();
         h->err = "host allocation failed";
         h->factored = false;
         return GDSW_ERR_BUDGET;

@@ -256,8 +256,6 @@ gdsw_status analyze(gdsw_handle_s *h, const gdsw_csr *A, const int32_t *part, in
 gdsw_status analyze_batch(gdsw_handle_s *h, int32_t count, const gdsw_csr *A, const int32_t *const *part,
                           const int32_t *n_parts, int32_t dpn, const double *const *Z, int32_t n_null,
                           const gdsw_options *opt);
-// whether n values are finite (over several threads when there are many)
-bool all_finite(const double *v, int64_t n);
 // nd.cpp: the nested-dissection supernodal structure of every A_i (needs
 // the local CSR of build_local)
 void build_nd(Symbolic &s);

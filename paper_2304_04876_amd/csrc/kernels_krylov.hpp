@@ -73,6 +73,13 @@ struct Sell {
     const int16_t *dcol;   // column - row (null with col)
 };
 
+// *bad = 1 if a value of A is not finite
+__global__ __launch_bounds__(256) void k_check_finite(const double *__restrict__ val, int64_t nnz, int *bad) {
+    bool found = false;
+    for (int64_t p = blockIdx.x * 256ll + threadIdx.x; p < nnz; p += 256ll * gridDim.x) found |= !isfinite(val[p]);
+    if (found) atomicExch(bad, 1);
+}
+
 // Values of A from CSR into the slices (slot j of a row at off + SELL_C j + the
 // row's place; the padding stays as it is)
 __global__ __launch_bounds__(SELL_C) void k_sell_values(const int32_t *__restrict__ rowptr,

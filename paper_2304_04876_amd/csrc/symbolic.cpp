@@ -28,7 +28,6 @@
 #include <functional>
 #include <map>
 #include <numeric>
-#include <thread>
 #include <queue>
 #include <stdexcept>
 #include <string>
@@ -1150,36 +1149,6 @@ gdsw_status analyze_batch(gdsw_handle_s *h, int32_t count, const gdsw_csr *A, co
         h->err = "host allocation failed in batch analysis";
         return GDSW_ERR_BUDGET;
     }
-}
-
-// (threads of its own, joined before the return, and this thread's share where
-// one cannot be had: a pool of the OpenMP runtime ends the process there)
-bool all_finite(const double *v, int64_t n) {
-    // values worth a thread (its start costs about 20 us, they about 120: 2.9 M
-    // values 890 us by one, 235 by four; 14.6 M 4.4 ms by one, 0.76 by eight)
-    constexpr int64_t GRAIN = 400000;
-    constexpr int MAX_T = 8;
-    const auto finite = [v](int64_t p0, int64_t p1) {
-        int bad = 0;
-        for (int64_t p = p0; p < p1; ++p) bad |= !std::isfinite(v[p]);
-        return bad == 0;
-    };
-    const int nt = int(std::max<int64_t>(1, std::min<int64_t>({n / GRAIN, MAX_T,
-                                                               int64_t(std::thread::hardware_concurrency())})));
-    bool ok[MAX_T];
-    std::thread t[MAX_T];
-    const auto share = [&](int k) { ok[k] = finite(n * k / nt, n * (k + 1) / nt); };
-    for (int k = 1; k < nt; ++k) {
-        try {
-            t[k] = std::thread(share, k);
-        } catch (const std::exception &) {   // (no thread, or no memory for one)
-            share(k);
-        }
-    }
-    share(0);
-    for (int k = 1; k < nt; ++k)
-        if (t[k].joinable()) t[k].join();
-    return std::all_of(ok, ok + nt, [](bool b) { return b; });
 }
 
 }  // namespace gdsw
