@@ -1138,9 +1138,11 @@ static void coarse_numeric(gdsw_handle_s *h, hipStream_t s) {
         for (int k = 0; k < S.nprob; ++k) nmax = std::max(nmax, S.prob_c0[k + 1] - S.prob_c0[k]);
         double *P = D.setup_scratch<double>(ST_GJ_P, GJ_NB * GJ_NB);
         double *W = D.setup_scratch<double>(ST_GJ_W, int64_t(nmax) * GJ_NB);
-        // the rows A(K, :): in E's place (used up by now) where they fit it
+        // the rows A(K, :): in E's place (used up by now) where they fit it (not
+        // beside interiors of a few rows); a capped handle whose E is smaller
+        // does without them, so that its cap is enough wherever it was
         const int64_t nkr = int64_t(nmax) * GJ_NB;
-        double *Kr = next >= nkr ? E : D.setup_scratch<double>(ST_GJ_K, nkr);
+        double *Kr = next >= nkr ? E : D.budget > 0 ? nullptr : D.setup_scratch<double>(ST_GJ_K, nkr);
         HIPCHK(hipMemsetAsync(d_status, 0, sizeof(int) * S.np, s));
         for (int k = 0; k < S.nprob; ++k) {
             const int nk = S.prob_c0[k + 1] - S.prob_c0[k];
@@ -1148,9 +1150,17 @@ static void coarse_numeric(gdsw_handle_s *h, hipStream_t s) {
             const int nt = (nk + 63) / 64;
             for (int k0 = 0; k0 < nk; k0 += GJ_NB) {
                 const int kb = std::min(GJ_NB, nk - k0);
-                hipLaunchKernelGGL(k_gj_panel, dim3(nt), dim3(256), 0, s, Ak, nk, k0, kb, P, W, Kr, int64_t(nmax),
-                                   d_status + (k % S.np));
-                hipLaunchKernelGGL(k_gj_update, dim3(nt, nt), dim3(256), 0, s, Ak, nk, k0, kb, W, Kr, int64_t(nmax), P);
+                int *st = d_status + (k % S.np);
+                if (Kr) {
+                    hipLaunchKernelGGL(k_gj_panel<true>, dim3(nt), dim3(256), 0, s, Ak, nk, k0, kb, P, W, Kr,
+                                       int64_t(nmax), st);
+                    hipLaunchKernelGGL(k_gj_update<true>, dim3(nt, nt), dim3(256), 0, s, Ak, nk, k0, kb, W, Kr,
+                                       int64_t(nmax), P);
+                } else {
+                    hipLaunchKernelGGL(k_gj_panel<false>, dim3(nt), dim3(256), 0, s, Ak, nk, k0, kb, P, W, Kr, 0, st);
+                    hipLaunchKernelGGL(k_gj_update<false>, dim3(nt, nt), dim3(256), 0, s, Ak, nk, k0, kb, W, Kr, 0, P);
+                    hipLaunchKernelGGL(k_gj_fix, dim3((nk + 255) / 256), dim3(256), 0, s, Ak, nk, k0, kb, W, P);
+                }
             }
         }
         hipLaunchKernelGGL(k_negate, dim3(nblocks(na0, 256, 65536)), dim3(256), 0, s, D.A0inv, na0);
@@ -1158,7 +1168,7 @@ static void coarse_numeric(gdsw_handle_s *h, hipStream_t s) {
         check_status(D, d_status, std::min(S.np, S.nprob), s, "coarse matrix inverse");
         D.setup_release(P, 8 * GJ_NB * GJ_NB);
         D.setup_release(W, 8 * size_t(nmax) * GJ_NB);
-        if (Kr != E) D.setup_release(Kr, 8 * size_t(nkr));
+        if (Kr && Kr != E) D.setup_release(Kr, 8 * size_t(nkr));
     }
     if (D.phi32) {
         hipLaunchKernelGGL(k_cast<float>, dim3(nblocks(nphi, 256, 65536)), dim3(256), 0, s, D.phi, D.phi32, nphi);

@@ -1722,7 +1722,9 @@ constexpr int GJ_LD = GJ_NB + 1;
 
 // Two launches per block K (a separate pivot kernel of one workgroup and
 // separate kernels for W and for storing it took 56, 48 and 16 us per block at
-// n = 2,863 beside the update's 48; now 23 + 31 us).
+// n = 2,863 beside the update's 48; now 23 + 31 us).  KR = false: a handle with a
+// memory cap and no room for the rows A(K, :), which the update then reads in
+// place, and k_gj_fix stores the block's rows and columns after it.
 
 // P = A_KK^{-1} by scalar sweeps, in every workgroup (one launch less, and no
 // workgroup waits for another's), then for 64 rows i per workgroup: W(i, :) =
@@ -1731,6 +1733,7 @@ constexpr int GJ_LD = GJ_NB + 1;
 // outside K.  A_KK itself is left for the update to replace (other workgroups
 // read it here).  Each sweep writes the other of two LDS copies, one barrier per
 // pivot; W is one ascending chain of products per value, by matrix instructions.
+template <bool KR>
 __global__ __launch_bounds__(256) void k_gj_panel(double *__restrict__ A, int n, int k0, int kb,
                                                   double *__restrict__ Pout, double *__restrict__ W,
                                                   double *__restrict__ Kr, int64_t ldk, int *__restrict__ status) {
@@ -1803,10 +1806,10 @@ __global__ __launch_bounds__(256) void k_gj_panel(double *__restrict__ A, int n,
         if (i >= n) continue;
         const double x = sW[r * GJ_LD + t];
         W[int64_t(i) * GJ_NB + t] = x;
-        if (t < kb && !(i >= k0 && i < k0 + kb)) A[int64_t(i) * n + k0 + t] = x;
+        if (KR && t < kb && !(i >= k0 && i < k0 + kb)) A[int64_t(i) * n + k0 + t] = x;
     }
     const int i = i0 + lane;
-    if (i < n) {
+    if (KR && i < n) {
         const bool inK = i >= k0 && i < k0 + kb;
 #pragma unroll
         for (int q = 0; q < 8; ++q) {
@@ -1822,7 +1825,8 @@ __global__ __launch_bounds__(256) void k_gj_panel(double *__restrict__ A, int n,
 // A(i, j) -= W(i, :) . Kr(:, j) for i, j outside K, A_KK = -P; 64x64 tiles, 16
 // rows per wavefront, by matrix instructions (one ascending chain per value,
 // subtracted once).  Bound by reading and writing A.
-__global__ __launch_bounds__(256) void k_gj_update(double *__restrict__ A, int n, int k0, int kb,
+template <bool KR>
+__global__ __launch_bounds__(256) void k_gj_update(double *A, int n, int k0, int kb,
                                                    const double *__restrict__ W, const double *__restrict__ Kr,
                                                    int64_t ldk, const double *__restrict__ P) {
     const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63, li = lane & 15, lg = lane >> 4;
@@ -1839,10 +1843,10 @@ __global__ __launch_bounds__(256) void k_gj_update(double *__restrict__ A, int n
     for (int q = 0; q < 8; ++q) {
         const int t = 4 * q + lg;
         const double a = W[int64_t(ir) * GJ_NB + t];   // (zero past kb)
-        const int64_t row = min(t, kb - 1) * ldk;
+        const double *row = KR ? Kr + min(t, kb - 1) * ldk : A + int64_t(k0 + min(t, kb - 1)) * n;
 #pragma unroll
         for (int u = 0; u < 4; ++u)
-            acc[u] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, Kr[row + min(j0 + 16 * u + li, n - 1)], acc[u], 0, 0, 0);
+            acc[u] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, row[min(j0 + 16 * u + li, n - 1)], acc[u], 0, 0, 0);
     }
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
@@ -1854,9 +1858,22 @@ __global__ __launch_bounds__(256) void k_gj_update(double *__restrict__ A, int n
             const int j = j0 + 16 * u + li;
             if (j >= n) continue;
             const bool jK = j >= k0 && j < k0 + kb;
-            if (iK && jK) A[int64_t(i) * n + j] = -P[(i - k0) * kb + (j - k0)];
+            if (KR && iK && jK) A[int64_t(i) * n + j] = -P[(i - k0) * kb + (j - k0)];
             else if (!iK && !jK) A[int64_t(i) * n + j] = old[u][v] - acc[u][v];
         }
+    }
+}
+
+// A(i, K) = W(i, :), A(K, i) = W(i, :)^T (i outside K), A_KK = -P
+__global__ __launch_bounds__(256) void k_gj_fix(double *__restrict__ A, int n, int k0, int kb,
+                                                const double *__restrict__ W, const double *__restrict__ P) {
+    const int i = blockIdx.x * 256 + threadIdx.x;
+    if (i >= n) return;
+    const bool inK = i >= k0 && i < k0 + kb;
+    for (int t = 0; t < kb; ++t) {
+        const double x = inK ? -P[(i - k0) * kb + t] : W[int64_t(i) * GJ_NB + t];
+        A[int64_t(i) * n + k0 + t] = x;
+        if (!inK) A[int64_t(k0 + t) * n + i] = x;
     }
 }
 
