@@ -1358,9 +1358,12 @@ static bool launch_ilu_phased(const Symbolic &S, Device &D, const double *r, con
 
 // Factors that do not stay in a workgroup's registers whole (more slots than
 // the register-resident kernels take, or more rows): the sweeps by blocks of
-// NT rows, for up to 24 slots where the rings of the iterates fit LDS.  The
-// next block's entries are loaded ahead where the registers hold them (512
-// threads; 1,024: up to 12 slots).
+// NT rows, for up to 24 slots where the rings of the iterates fit LDS, by
+// instances of 6, 12, 16 and 24 slots (13 and 15 slots in the instance of 24, us,
+// five sweeps, in that of 16: 27-point ILU(0) on 27 subdomains of 2,744 rows FP64
+// 68 / 50, FP32 38 / 30; red-black ILU(1) on 27 of 5,632 rows 119 / 91, 71 / 57).
+// The next block's entries are loaded ahead where the registers hold them (512
+// threads; 1,024: up to 12 slots, below FP64 up to 16).
 template <typename VT, int NT>
 static bool launch_ilu_blocks(const Symbolic &S, Device &D, const double *r, const Skip &sk, hipStream_t s,
                               const Device::SizeClass &c) {
@@ -1383,6 +1386,7 @@ static bool launch_ilu_blocks(const Symbolic &S, Device &D, const double *r, con
                            int(ring), kc)
         if (K <= 6) GDSW_ILU_BLOCKS(6, true);
         else if (K <= 12) GDSW_ILU_BLOCKS(12, true);
+        else if (K <= 16) GDSW_ILU_BLOCKS(16, (NT == 512 || sizeof(VT) < 8));
         else GDSW_ILU_BLOCKS(24, NT == 512);
 #undef GDSW_ILU_BLOCKS
         return true;
@@ -1400,7 +1404,9 @@ static bool launch_ilu_blocks(const Symbolic &S, Device &D, const double *r, con
 // and ILU(3) factors past the caches or with idle rows (R rows a thread, a
 // subdomain needing fewer than 4/5 of them).  With three: for few slots to
 // read again, FP64 up to 12 a triangle (or every thread's rows full), FP32, and
-// 16-bit entries from 13 on.
+// 16-bit entries from 13 on; with four FP32 with 13 to 16 and every thread's rows
+// full (red-black ILU(1), 64 subdomains of 5,632 rows: 52 / 56 us; five sweeps
+// 63 / 62).
 // Measured (us, this form / by blocks; 27, 125 and 512 subdomains of 5,632 rows,
 // 64 of 2,592): ILU(2) FP64 two sweeps 41 / 55, 45 / 60, 155 / 146, 32 / 33,
 // three 57 / 62, 65 / 67, 203 / 151, 45 / 37; ILU(3) FP32 two sweeps 38 / 54,
@@ -1425,6 +1431,7 @@ static bool launch_ilu_hold(const Symbolic &S, Device &D, const double *r, const
         const auto ahead = [&](int R) {
             const bool filled = 5 * need >= 4 * R;
             if (sweeps == 2) return !f64 || (K <= 12 ? filled && cached : filled || cached);
+            if (sweeps == 4) return sizeof(VT) == 4 && K > 12 && K <= 16 && need == R && cached;
             return sweeps == 3 && filled && cached && (f64 ? K <= 12 || need == R : sizeof(VT) == 4 || K > 12);
         };
 #define GDSW_ILU_HOLD(RR)                                                                                     \

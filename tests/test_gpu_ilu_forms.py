@@ -4,8 +4,11 @@ available wherever they were, whatever the number of slots, and give the bits of
 the streaming form."""
 import sys
 
+import types
+
 import numpy as np
 import pytest
+import scipy.sparse as sp
 
 from paper_2304_04876_amd import binding as B
 from paper_2304_04876_amd import problems as P
@@ -45,3 +48,33 @@ def test_more_than_24_slots(prec, sweeps):
 def test_few_sweeps(N, boxes, ns, level, sweeps, prec):
     _forms_agree(P.poisson3d(N, boxes), ns, local_prec=prec, basis_prec=B.FP64 if prec == B.FP64 else B.FP32,
                  jacobi_sweeps=sweeps, ilu_level=level)
+
+
+def _stencil27(N, boxes):
+    """The 27-point stencil on the Poisson problem's grid and boxes."""
+    pr = P.poisson3d(N, boxes)
+    T = sp.diags([np.ones(N - 1), np.ones(N), np.ones(N - 1)], [-1, 0, 1])
+    A = (27.0 * sp.eye(N ** 3) - sp.kron(sp.kron(T, T), T)).tocsr()
+    A.sort_indices()
+    return types.SimpleNamespace(A=A, part=pr.part, n_parts=pr.n_parts, n=pr.n, dpn=1)
+
+
+def _red_black(N, boxes):
+    """The Poisson problem with the nodes of one colour numbered first (entries
+    reach across half of a subdomain)."""
+    pr = P.poisson3d(N, boxes)
+    i = np.arange(pr.n)
+    q = np.argsort((i % N + i // N % N + i // N ** 2) % 2, kind="stable")
+    A = pr.A.tocsr()[q][:, q].tocsr()
+    A.sort_indices()
+    return types.SimpleNamespace(A=A, part=np.asarray(pr.part)[q], n_parts=pr.n_parts, n=pr.n, dpn=1)
+
+
+# 13 and 15 slots a triangle; three and four sweeps take the held form where
+# every thread's rows are full (1,960 rows), five always the blocks
+@pytest.mark.parametrize("prec", [B.FP64, B.FP32, B.FP16, B.BF16])
+@pytest.mark.parametrize("sweeps", [2, 3, 4, 5])
+@pytest.mark.parametrize("make,level", [(lambda: _stencil27(14, 2), 0), (lambda: _red_black(20, (1, 1, 4)), 1)])
+def test_13_to_16_slots(make, level, sweeps, prec):
+    _forms_agree(make(), local_prec=prec, basis_prec=B.FP64 if prec == B.FP64 else B.FP32, jacobi_sweeps=sweeps,
+                 ilu_level=level)
