@@ -413,8 +413,8 @@ gdsw_status gdsw_slot_finish(gdsw_handle h, int32_t slot, gdsw_solve_info *info,
 
 /* Autotuner: times every launch configuration of the local-solve kernel
  * (ILU(0): sweeps that read the factors once, held in registers whole or by
- * blocks of rows, with 512 or 1024 threads, streaming sweeps with 256 or 512
- * threads; exact: band solves with 256, 512 or 1024
+ * blocks of rows, or hold each row's first entries, with 512 or 1024 threads,
+ * streaming sweeps with 256 or 512 threads; exact: band solves with 256, 512 or 1024
  * threads, one workgroup per subdomain or as persistent workgroups drawing
  * subdomains from a work counter), both coarse GEMV variants, and the whole
  * apply with the coarse part on the caller's stream after the local solves
